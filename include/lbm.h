@@ -104,10 +104,7 @@ lbm_status lbm_set_inflow(lbm_ctx *ctx, double xc, double yc, double diameter, d
 /* Tile shape of the step kernel: (tx, ty) in {(32, 4), (32, 8), (32, 16), (64, 4), (64, 8)}
  * cells per workgroup, zchunk >= 1 z planes per workgroup, or 0 to let the library choose
  * it from the number of workgroups the device holds at once.  Default: (64, 4, 0) for
- * nx >= 64, (32, 8, 0) otherwise.  With free-slip x or y faces a step is several launches:
- * the interior tiles (no cell or ring cell on a wall), the tiles along the x walls and along
- * the y walls (with FP16 storage: along each of the -x, +x, -y and +y walls), and the
- * corners; with zchunk = 0 each gets its own z chunk.
+ * nx >= 64, (32, 8, 0) otherwise.
  * Results do not depend on the tiling; this is a tuning hook.  LBM_EINVAL for other shapes
  * or zchunk < 0. */
 lbm_status lbm_set_tiling(lbm_ctx *ctx, int tx, int ty, int zchunk);
@@ -251,17 +248,14 @@ lbm_status lbm_selftest_collide_host(const lbm_params *params, const double *fr,
                                      const double *grad_phi, const double *grad_rho, double *out_r, double *out_b);
 
 /* Diagnostic, not used by lbm_step: how a step with tile shape tx x ty (32x4, 32x8, 64x4,
- * 64x8 or 32x16) distributes the tiles of a lattice with these parameters over its launches.
- * counts (caller-owned, 3 * tiles_x * tiles_y ints, tiles_x = ceil(nx/tx), tiles_y =
- * ceil(ny/ty), tile (i, j) at j * tiles_x + i) receives for each tile how many times the launch
- * over all tiles (block 0), over the interior tiles (block 1) and over the frame tiles (block 2)
- * would process it.  Without lateral walls one launch covers all tiles; with free-slip x or y
- * faces the interior tiles (none of whose cells or ring cells lies on a wall) take the plain
- * pull, and the frame is up to three launches (x edges, y edges, corners), five with FP16
- * storage (one per wall along the edges, one for the corners), with the instances that
- * reflect at those walls.  LBM_EDEVICE if a tile falls
- * outside the lattice or touches a wall its launch does not reflect at (an internal error);
- * LBM_EINVAL for invalid parameters or shapes. */
+ * 64x8 or 32x16) treats the tiles of a lattice with these parameters.  counts (caller-owned,
+ * 3 * tiles_x * tiles_y ints, tiles_x = ceil(nx/tx), tiles_y = ceil(ny/ty), tile (i, j) at
+ * j * tiles_x + i) receives for each tile how many times the step processes it as a tile of a
+ * lattice without lateral walls (block 0), as an interior tile beside free-slip x or y faces (none
+ * of its cells or ring cells lies on a wall: it takes the plain population loads, block 1) and as a
+ * frame tile (it takes the loads that mirror at the walls, block 2).  One launch covers all tiles.
+ * LBM_EDEVICE if an interior tile touches a wall (an internal error); LBM_EINVAL for invalid
+ * parameters or shapes. */
 lbm_status lbm_selftest_tile_sets_host(const lbm_params *params, int tx, int ty, int *counts);
 
 #ifdef __cplusplus

@@ -41,8 +41,6 @@ struct lbm_ctx {
   long long step = 0;
   bool initialised = false;
   int tx = 0, ty = 0, zchunk = 0;  // 0: chosen at the first step (choose_tiling, auto_zchunk)
-  int zchunk_set[kCorners + 1] = {};  // with lateral walls and an automatic zchunk: the z
-                                      // chunk of each tile set's launch (0: zchunk)
   bool in_batch = false;           // advanced only by lbm_batch_step
   bool frozen = false;             // a batch case found unstable: no longer stepped
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -277,7 +275,6 @@ extern "C" lbm_status lbm_set_tiling(lbm_ctx* c, int tx, int ty, int zchunk) {
   c->tx = tx;
   c->ty = ty;
   c->zchunk = zchunk;
-  for (int& z : c->zchunk_set) z = 0;
   return LBM_OK;
 }
 
@@ -353,38 +350,15 @@ static int auto_zchunk(const lbm_ctx* c) {
   return zchunk_for(c, (long long)((G.nx + c->tx - 1) / c->tx) * ((G.ny + c->ty - 1) / c->ty));
 }
 
-static void fill_step_args(const lbm_ctx* c, int cur, int out_cur, StepArgs& s);
-
 static void choose_tiling(lbm_ctx* c) {
   if (c->tx == 0) {
-    // measured on MI355X: 64 x 4 tiles on rows of 64 cells or more, 32 x 8 otherwise; with
-    // lateral walls 64 x 4 and 32 x 8 are within 0.3 % of each other on the jet
+    // measured on MI355X: 64 x 4 tiles on rows of 64 cells or more, 32 x 8 otherwise
     // (lbm_autotune times the shapes for a given lattice)
     const bool wide = c->geo.nx >= 64;
     c->tx = wide ? 64 : 32;
     c->ty = wide ? 4 : 8;
   }
-  if (c->zchunk < 1) {
-    c->zchunk = auto_zchunk(c);
-    for (int& z : c->zchunk_set) z = 0;
-    if (c->geo.wall_x || c->geo.wall_y) {
-      // the interior and the parts of the frame run as launches one after the other: each is
-      // chunked in z to fill the device by itself
-      StepArgs s{};
-      fill_step_args(c, 0, 0, s);
-      int sets[kCorners + 1];
-      const int nsets = wall_tile_sets((int)c->p.storage, sets);
-      for (int k = 0; k < nsets; ++k) {
-        s.tile_set = sets[k];
-        c->zchunk_set[sets[k]] = zchunk_for(c, tiles_in_set(s));
-      }
-    }
-  }
-}
-
-static void set_zchunk(const Geo& G, int zchunk, StepArgs& s) {
-  s.zchunk = zchunk;
-  s.nchunks = (G.nz + zchunk - 1) / zchunk;
+  if (c->zchunk < 1) c->zchunk = auto_zchunk(c);
 }
 
 // Arguments of the step kernel for the state of parity cur (outlet record out_cur).
@@ -404,7 +378,6 @@ static void fill_step_args(const lbm_ctx* c, int cur, int out_cur, StepArgs& s) 
   s.nchunks = (G.nz + c->zchunk - 1) / c->zchunk;
   // interior rectangle: tiles whose own and ring cells are all off the lateral walls, i.e.
   // tile index >= 1 and (index + 1) * tile width <= n - 2 along each axis that has walls
-  s.tile_set = kAllTiles;
   s.tx_lo = 0;
   s.tx_hi = s.tiles_x;
   s.ty_lo = 0;
@@ -446,22 +419,7 @@ static lbm_status enqueue_one(lbm_ctx* c) {
   StepArgs s{};
   choose_tiling(c);
   fill_step_args(c, c->cur, c->out_cur, s);
-  hipError_t e = hipSuccess;
-  if (G.wall_x || G.wall_y) {
-    // the interior tiles with the plain pull, the edges and corners of the frame with the
-    // instances that reflect at their walls
-    int sets[kCorners + 1];
-    const int nsets = wall_tile_sets((int)c->p.storage, sets);
-    for (int k = 0; k < nsets && e == hipSuccess; ++k) {
-      const int set = sets[k];
-      s.tile_set = set;
-      if (tiles_in_set(s) == 0) continue;
-      set_zchunk(G, c->zchunk_set[set] > 0 ? c->zchunk_set[set] : c->zchunk, s);
-      e = launch_step((int)c->p.storage, s, c->tx, c->ty, c->stream);
-    }
-  } else {
-    e = launch_step((int)c->p.storage, s, c->tx, c->ty, c->stream);
-  }
+  hipError_t e = launch_step((int)c->p.storage, s, c->tx, c->ty, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "step kernel");
   if (G.inflow) {
     e = launch_inflow((int)c->p.storage, s, c->stream);
@@ -722,8 +680,7 @@ extern "C" lbm_status lbm_load_state(lbm_ctx* c, const void* src, size_t bytes) 
 // lbm_batch_step call.
 struct BatchGroup {
   int storage = 0, tx = 0, ty = 0;
-  int lat = 0;                          // reflection mode of the instance (lat_mode_of)
-  int tile_set = kAllTiles;             // the tiles of each case the group's launch covers
+  bool walls = false;                   // lateral free-slip walls
   std::vector<int> cases;               // indices into lbm_batch::c
   StepArgs* d_args[2] = {nullptr, nullptr};  // device tables for parity 0 and 1
   int* d_first = nullptr;               // device block offsets (ncases + 1)
@@ -844,39 +801,22 @@ static void batch_tiling(lbm_batch* b) {
 
 static lbm_status build_groups(lbm_batch* b) {
   free_groups(b);
-  auto add = [&](int k, int lat, int set) {
+  for (int k = 0; k < (int)b->c.size(); ++k) {
     const lbm_ctx* c = b->c[k];
+    if (c->frozen) continue;
+    const bool walls = c->geo.wall_x || c->geo.wall_y;
     BatchGroup* g = nullptr;
     for (auto& x : b->groups)
-      if (x.storage == (int)c->p.storage && x.tx == c->tx && x.ty == c->ty && x.lat == lat && x.tile_set == set) g = &x;
+      if (x.storage == (int)c->p.storage && x.tx == c->tx && x.ty == c->ty && x.walls == walls) g = &x;
     if (!g) {
       b->groups.emplace_back();
       g = &b->groups.back();
       g->storage = (int)c->p.storage;
       g->tx = c->tx;
       g->ty = c->ty;
-      g->lat = lat;
-      g->tile_set = set;
+      g->walls = walls;
     }
     g->cases.push_back(k);
-  };
-  for (int k = 0; k < (int)b->c.size(); ++k) {
-    const lbm_ctx* c = b->c[k];
-    if (c->frozen) continue;
-    if (c->geo.wall_x || c->geo.wall_y) {
-      // with lateral walls: the interior tiles in a plain group, each part of the frame in the
-      // group of its reflection mode
-      StepArgs s{};
-      fill_step_args(c, 0, 0, s);
-      int sets[kCorners + 1];
-      const int nsets = wall_tile_sets((int)c->p.storage, sets);
-      for (int m = 0; m < nsets; ++m) {
-        s.tile_set = sets[m];
-        if (tiles_in_set(s) > 0) add(k, lat_mode_of(sets[m], true), sets[m]);
-      }
-    } else {
-      add(k, 0, kAllTiles);
-    }
   }
   for (auto& g : b->groups) {
     const int n = (int)g.cases.size();
@@ -887,11 +827,10 @@ static lbm_status build_groups(lbm_batch* b) {
       for (int par = 0; par < 2; ++par) {
         StepArgs s{};
         fill_step_args(c, par, par, s);
-        s.tile_set = g.tile_set;
         h[par].push_back(s);
       }
       const StepArgs& s = h[0].back();
-      const long long blocks = (long long)tiles_in_set(s) * s.nchunks;
+      const long long blocks = (long long)s.tiles_x * s.tiles_y * s.nchunks;
       first[j + 1] = first[j] + (int)((blocks + 7) / 8 * 8);
     }
     g.nblocks = first[n];
@@ -1011,7 +950,7 @@ extern "C" lbm_status lbm_batch_step(lbm_batch* b, int nsteps) {
     }
     for (const auto& g : b->groups) {
       const hipError_t e = launch_batch(g.storage, g.d_args[par], g.d_first, (int)g.cases.size(), g.nblocks, init,
-                                        g.tx, g.ty, g.lat, b->stream);
+                                        g.tx, g.ty, g.walls, b->stream);
       if (e != hipSuccess) return batch_fail(b, LBM_EDEVICE, std::string("batch step kernel: ") + hipGetErrorString(e));
     }
     for (const auto& g : b->inflows) {
@@ -1169,30 +1108,17 @@ extern "C" lbm_status lbm_selftest_tile_sets_host(const lbm_params* params, int 
   const int nt = s.tiles_x * s.tiles_y;
   for (int k = 0; k < 3 * nt; ++k) counts[k] = 0;
   const bool walls = tmp.geo.wall_x || tmp.geo.wall_y;
-  // the launches enqueue_one makes: one over all tiles without walls, else the interior and
-  // the edges and corners of the frame for the storage type (reported together as the frame)
-  int sets[kCorners + 1];
-  const int nsets = walls ? wall_tile_sets((int)tmp.p.storage, sets) : 1;
-  if (!walls) sets[0] = kAllTiles;
-  for (int m = 0; m < nsets; ++m) {
-    const int set = sets[m];
-    const int b = set == kAllTiles ? 0 : (set == kInteriorTiles ? 1 : 2);
-    s.tile_set = set;
-    const int n = tiles_in_set(s);
-    for (int t = 0; t < n; ++t) {
-      int i = -1, j = -1;
-      tile_of(s, t, i, j);
-      if (i < 0 || i >= s.tiles_x || j < 0 || j >= s.tiles_y) return fail(nullptr, LBM_EDEVICE, "tile out of range");
-      // the walls (bits of wall_flags) that the tile's cells, and its ring cells inside the
-      // lattice, lie on must be among those its instance reflects at (a ring cell beyond a
-      // wall, wrapped to the opposite side, is never read: there the stencil takes the
-      // boundary cell)
-      const int x0 = i * tx, y0 = j * ty;
-      const int touched = (tmp.geo.wall_x && x0 == 0 ? 1 : 0) | (tmp.geo.wall_x && x0 + tx > tmp.geo.nx - 2 ? 2 : 0) |
-                          (tmp.geo.wall_y && y0 == 0 ? 4 : 0) | (tmp.geo.wall_y && y0 + ty > tmp.geo.ny - 2 ? 8 : 0);
-      if (walls && (touched & ~lat_mode_of(set, true)) != 0) return fail(nullptr, LBM_EDEVICE, "tile in the wrong set");
-      counts[b * nt + j * s.tiles_x + i]++;
-    }
+  // the step's block-to-tile map, tile by tile
+  for (int t = 0; t < nt; ++t) {
+    const int j = t / s.tiles_x, i = t - j * s.tiles_x;
+    const int b = !walls ? 0 : (interior_tile(s, i, j) ? 1 : 2);
+    // no cell, and no ring cell inside the lattice, of an interior tile lies on a wall (a ring
+    // cell beyond a wall is never read: there the stencil takes the boundary cell)
+    const int x0 = i * tx, y0 = j * ty;
+    const bool on_wall = (tmp.geo.wall_x && (x0 == 0 || x0 + tx > tmp.geo.nx - 2)) ||
+                         (tmp.geo.wall_y && (y0 == 0 || y0 + ty > tmp.geo.ny - 2));
+    if (b == 1 && on_wall) return fail(nullptr, LBM_EDEVICE, "a tile on a wall takes the plain loads");
+    counts[b * nt + t]++;
   }
   return LBM_OK;
 }

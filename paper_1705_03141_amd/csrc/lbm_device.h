@@ -82,6 +82,14 @@ __device__ __forceinline__ int wrap(int v, int n) {
   return v < 0 ? v + n : v;
 }
 
+// The cell a position beyond the walls of an axis of n cells mirrors to (half a cell outside the
+// outer planes: -1 -> 0, -2 -> 1, n -> n - 1); clamped into the lattice further out, where
+// nothing that is used reads it.
+__device__ __forceinline__ int mirror(int v, int n) {
+  v = v < 0 ? -1 - v : (v >= n ? 2 * n - 1 - v : v);
+  return v < 0 ? 0 : (v >= n ? n - 1 : v);
+}
+
 __device__ __forceinline__ bool is_inflow(const Geo& G, int x, int y, int z) {
   if (!G.inflow || z != 0) return false;
   const float dx = (float)x - G.xc, dy = (float)y - G.yc;

@@ -105,60 +105,62 @@ __device__ __forceinline__ void store_f32(float v, rsrc_t r, unsigned vo, int so
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)vo, so, 0);
 }
 
-// Offsets, in bytes, of the 3 x 3 neighbourhood of column (x, y) within one population plane.
-template <typename T>
-__device__ __forceinline__ void column_offsets(const Geo& G, int x, int y, unsigned (&o)[3][3]) {
-  const int xs[3] = {x == 0 ? G.nx - 1 : x - 1, x, x == G.nx - 1 ? 0 : x + 1};
-  const int ys[3] = {y == 0 ? G.ny - 1 : y - 1, y, y == G.ny - 1 ? 0 : y + 1};
+// Offsets, in bytes, of the 3 x 3 neighbourhood of column (x, y) within one population plane,
+// plus `from`.  WALLS: beyond a free-slip wall of the lattice the neighbour is the boundary column itself.
+template <typename T, bool WALLS>
+__device__ __forceinline__ void column_offsets(const Geo& G, int x, int y, int from, unsigned (&o)[3][3]) {
+  const bool wx = WALLS && G.wall_x, wy = WALLS && G.wall_y;
+  const int xs[3] = {x == 0 ? (wx ? 0 : G.nx - 1) : x - 1, x, x == G.nx - 1 ? (wx ? x : 0) : x + 1};
+  const int ys[3] = {y == 0 ? (wy ? 0 : G.ny - 1) : y - 1, y, y == G.ny - 1 ? (wy ? y : 0) : y + 1};
 #pragma unroll
   for (int b = 0; b < 3; ++b)
 #pragma unroll
-    for (int a = 0; a < 3; ++a) o[b][a] = (unsigned)((ys[b] * G.nx + xs[a]) * (int)sizeof(T));
-}
-
-// Bit of wall_flags for the wall a source offset D along AXIS (0: x, 1: y) crosses.
-template <int AXIS, int D>
-constexpr int wall_bit() {
-  return (AXIS == 0 ? 0 : 2) + (D < 0 ? 0 : 1);
-}
-
-// Lateral reflection of a source offset at a cell with wall flags wf (wall_flags): true where
-// the source (dx, dy) lies beyond a free-slip wall in x (AXIS 0) or y (AXIS 1).  LAT is the
-// instance's reflection mode, the walls it reflects at in the bits of wall_flags; a wall it
-// leaves out never reflects.
-template <int AXIS, int D, int LAT>
-__device__ __forceinline__ bool reflects(int wf) {
-  if constexpr (D == 0 || ((LAT >> wall_bit<AXIS, D>()) & 1) == 0) return false;
-  else return (wf >> wall_bit<AXIS, D>()) & 1;
-}
-
-// Whether a pull direction with source offset (DX, DY) can reflect at a lateral wall in
-// reflection mode LAT.
-template <int LAT, int DX, int DY>
-constexpr bool lat_dir() {
-  return (DX != 0 && ((LAT >> wall_bit<0, DX>()) & 1)) || (DY != 0 && ((LAT >> wall_bit<1, DY>()) & 1));
+    for (int a = 0; a < 3; ++a) o[b][a] = (unsigned)((ys[b] * G.nx + xs[a]) * (int)sizeof(T) + from);
 }
 
 // Issue the 27 population loads of a pull in mode MODE.  slab[k] covers the 27 population
-// planes of source plane z - 1 + k; the raw word of direction i is left in ld[i].  With
-// lateral walls (LAT != 0) a source beyond a wall is the boundary cell and the mirrored
-// population (reading R9), chosen per lane: its population plane then enters the per-lane
-// offset.
-template <typename T, int MODE, int LAT>
-__device__ __forceinline__ void issue_pull(const rsrc_t (&slab)[3], int plane_bytes, const unsigned (&o)[3][3], int wf,
+// planes of source plane z - 1 + k; the raw word of direction i is left in ld[i].
+template <typename T, int MODE>
+__device__ __forceinline__ void issue_pull(const rsrc_t (&slab)[3], int plane_bytes, const unsigned (&o)[3][3],
                                            typename Word<T>::W (&ld)[Q]) {
   static_for<0, Q>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr Src s = resolve<i, MODE>();
-    if constexpr (!lat_dir<LAT, s.dx, s.dy>()) {
-      ld[i] = Word<T>::load(slab[s.dz + 1], o[s.dy + 1][s.dx + 1], s.j * plane_bytes);
-    } else {
-      const bool rx = reflects<0, s.dx, LAT>(wf), ry = reflects<1, s.dy, LAT>(wf);
-      constexpr int jx = mirror_x(s.j), jy = mirror_y(s.j), jxy = mirror_x(mirror_y(s.j));
-      const unsigned col = rx ? (ry ? o[1][1] : o[s.dy + 1][1]) : (ry ? o[1][s.dx + 1] : o[s.dy + 1][s.dx + 1]);
-      const int j = rx ? (ry ? jxy : jx) : (ry ? jy : s.j);
-      ld[i] = Word<T>::load(slab[s.dz + 1], col + (unsigned)(j * plane_bytes), 0);
-    }
+    ld[i] = Word<T>::load(slab[s.dz + 1], o[s.dy + 1][s.dx + 1], s.j * plane_bytes);
+  });
+}
+
+// The same beside lateral free-slip walls.  A population whose source lies beyond a wall is
+// the boundary cell's mirrored population (reading R9): the columns o are already those of the
+// boundary cell (column_offsets<T, true>), and what remains is the index of the mirrored
+// population, which differs per lane.  wf holds the cell's wall flags; a lane's correction is
+// the difference of the two indices, kept or dropped by a mask, so that a direction costs one
+// AND and one add per axis (selecting the index and multiplying it by the plane's size per lane
+// cost about three times as much and made the instances spill).  The differences are at least
+// -kMirrorSpan planes, so the descriptors start that many planes early and the lane offsets
+// stay positive: the hardware checks a lane's offset against the descriptor's length before the
+// scalar offset is added.
+constexpr int kMirrorSpan = 6;
+
+template <typename T, int MODE>
+__device__ __forceinline__ void issue_pull_walls(const rsrc_t (&slab)[3], int plane_bytes, const unsigned (&o)[3][3],
+                                                 int wf, typename Word<T>::W (&ld)[Q]) {
+  const unsigned at[2][2] = {{0u - (wf & 1), 0u - ((wf >> 1) & 1)}, {0u - ((wf >> 2) & 1), 0u - ((wf >> 3) & 1)}};
+  static_for<0, Q>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    constexpr Src s = resolve<i, MODE>();
+    constexpr int jx = mirror_x(s.j), jy = mirror_y(s.j), jxy = mirror_x(jy);
+    static_assert(jx - s.j <= kMirrorSpan && s.j - jx <= kMirrorSpan && jy - s.j <= kMirrorSpan &&
+                      s.j - jy <= kMirrorSpan && jxy - s.j <= kMirrorSpan && s.j - jxy <= kMirrorSpan,
+                  "mirrored population further than the descriptors reach");
+    unsigned v = o[s.dy + 1][s.dx + 1];
+    const unsigned mx = s.dx == 0 ? 0u : at[0][s.dx > 0], my = s.dy == 0 ? 0u : at[1][s.dy > 0];
+    if constexpr (s.dx != 0) v += mx & (unsigned)((jx - s.j) * plane_bytes);
+    if constexpr (s.dy != 0) v += my & (unsigned)((jy - s.j) * plane_bytes);
+    // at a corner both mirror: the two differences do not simply add
+    if constexpr (s.dx != 0 && s.dy != 0 && jxy - jx - jy + s.j != 0)
+      v += (mx & my) & (unsigned)((jxy - jx - jy + s.j) * plane_bytes);
+    ld[i] = Word<T>::load(slab[s.dz + 1], v, s.j * plane_bytes);
   });
 }
 
@@ -180,9 +182,9 @@ __device__ __forceinline__ float div_nc(float a, float b) {
   return a / b;
 }
 
-template <typename T, int MODE, bool WANT_DF, int SX, int LAT>
+template <typename T, int MODE, bool WANT_DF, int SX>
 __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], const float4* const (&S)[3], const float2* const (&W)[3],
-                                            int idx0, int wf, const PullConst& C, float& rho, float& rho_r, float& rho_b,
+                                            int idx0, const PullConst& C, float& rho, float& rho_r, float& rho_b,
                                             float& e_new, float (&df)[Q], float& shift_out, float& drho_out) {
   const float4 me = S[1][idx0 + SX + 1];
   const float e_self = me.x, a_self = me.y, b_self = me.z;
@@ -209,23 +211,12 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
     constexpr int off = (s.dy + 1) * SX + s.dx + 1;
     constexpr int sh = shell_of(i);
     constexpr bool self_src = s.dx == 0 && s.dy == 0 && s.dz == 0;  // bounce-back
-    constexpr bool lat = lat_dir<LAT, s.dx, s.dy>();
-    // lateral wall: the source is the boundary cell along a reflected axis, and the velocity
-    // component normal to that wall is reversed
-    bool rx = false, ry = false;
-    int offl = off;
-    if constexpr (lat) {
-      rx = reflects<0, s.dx, LAT>(wf);
-      ry = reflects<1, s.dy, LAT>(wf);
-      offl = ((ry ? 0 : s.dy) + 1) * SX + (rx ? 0 : s.dx) + 1;
-    }
-    const float4 src = S[s.dz + 1][idx0 + offl];
-    const float2 w = W[s.dz + 1][idx0 + offl];
+    const float4 src = S[s.dz + 1][idx0 + off];
+    const float2 w = W[s.dz + 1][idx0 + off];
     // c_j . w of the source from its non-zero components (a sum started at 0.0f would cost
     // one more add: 0 + x is not folded because of the sign of zero)
-    const bool px = (s.ccx > 0) != rx, py = (s.ccy > 0) != ry;
-    const float wy = py ? w.x : -w.x, wz = s.ccz > 0 ? w.y : -w.y;
-    float cw = s.ccx != 0 ? (px ? src.w : -src.w) : (s.ccy != 0 ? wy : wz);
+    const float wy = s.ccy > 0 ? w.x : -w.x, wz = s.ccz > 0 ? w.y : -w.y;
+    float cw = s.ccx != 0 ? (s.ccx > 0 ? src.w : -src.w) : (s.ccy != 0 ? wy : wz);
     if constexpr (s.ccx != 0 && s.ccy != 0) cw = add_nc(cw, wy);
     if constexpr ((s.ccx != 0 || s.ccy != 0) && s.ccz != 0) cw = add_nc(cw, wz);
     float d, inc;
@@ -303,7 +294,7 @@ struct PlaneState {
   }
 };
 
-template <typename T, int TX, int TY, bool INIT, int LAT>
+template <typename T, int TX, int TY, bool INIT, bool WALLS>
 #ifndef LBM_STEP_WAVES_PER_EU
 #define LBM_STEP_WAVES_PER_EU 2
 #endif
@@ -331,13 +322,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // Issue order of a pass's loads (measured): with FP32 populations the staged scalars go
   // first, with 16-bit populations after the population loads.  Their LDS write waits until
   // the pull is complete, so that the pull consumes each population load as soon as it and
-  // the older loads have arrived, rather than after all of them.  The instances that spill
-  // (the corner instance, and with FP16 storage every reflecting one) keep the scalars first
-  // and their LDS write before the pull, so that the staged values are not live across it
-  // (FP16 jet between walls: 4.47 against 4.81 ms per step).
-  constexpr bool kHalfWall = std::is_same<T, _Float16>::value && LAT != 0;
-  constexpr bool kStoreLate = LAT != 15 && !kHalfWall;
-  constexpr bool kStageFirst = LAT == 15 || sizeof(T) == 4 || kHalfWall;
+  // the older loads have arrived, rather than after all of them.
+  constexpr bool kStageFirst = sizeof(T) == 4;
 
   const Geo& G = A.geo;
   const bool zper = G.face_lo == FACE_PERIODIC;
@@ -352,14 +338,13 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // block L of nb -> (z chunk, tile); XCD x receives blocks x, x + 8, ...: give it a
   // contiguous range (nb and the first block of the range are multiples of 8 when remapped)
   if ((nb & 7) == 0) L = (L & 7) * (nb >> 3) + (L >> 3);
-  const int ntiles = tiles_in_set(A);
+  const int ntiles = A.tiles_x * A.tiles_y;
   const int chunk = L / ntiles, tile = L - chunk * ntiles;
   if (chunk >= A.nchunks) return;  // padding block of a batch (the whole block leaves)
   // a lattice of a batch that went unstable is not stepped further (the flag is read once per
   // workgroup, before any barrier; the whole workgroup leaves)
   if (A.skip_unstable && __hip_atomic_load(A.unstable, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-  int txi, tyi;
-  tile_of(A, tile, txi, tyi);
+  const int tyi = tile / A.tiles_x, txi = tile - tyi * A.tiles_x;
   const int x0 = txi * TX, y0 = tyi * TY;
   const int z0 = chunk * A.zchunk, z1 = min(z0 + A.zchunk, G.nz);
 
@@ -377,17 +362,34 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   const int rgx = wrap(x0 + rx, G.nx), rgy = wrap(y0 + ry, G.ny);
   const int rcol = rgy * G.nx + rgx;
   const int sR = (ry + 2) * SX + rx + 2, dR = (ry + 1) * DX + rx + 1;
-  // lateral wall flags of the own and the ring cell (0 without lateral walls)
-  // (only the walls of the instance's mode: the tiles it serves touch no others)
-  constexpr int kWallMask = LAT;
-  const int wfI = LAT ? wall_flags(G, gx, gy) & kWallMask : 0, wfR = LAT ? wall_flags(G, rgx, rgy) & kWallMask : 0;
-  // staged cells
+  // Lateral walls: the wall flags of the own and the ring cell, and whether the tile has any
+  // cell or ring cell on a wall (uniform over the workgroup; the others take the plain loads).
+  // One word: the flags of the own cell (bits 0-3), of the ring cell (4-7), and from bit 8 two
+  // bits per staged cell, w_x and w_y of which change sign.
+  int walls = WALLS ? wall_flags(G, gx, gy) | wall_flags(G, rgx, rgy) << 4 : 0;
+  const bool frame = WALLS && !interior_tile(A, txi, tyi);
+  // Staged cells.  A cell beyond a wall is staged as the mirror image of the cell inside: its
+  // scalars with the normal component of w reversed, which is what a pull across the wall reads
+  // (R9), so the pull itself needs no case for walls.
   unsigned stOff[KS];  // byte offsets in a scalar plane
 #pragma unroll
   for (int k = 0; k < KS; ++k) {
     const int idx = min(tid + k * NT, NS - 1);
-    const int sx = idx % SX, sy = idx / SX;
-    stOff[k] = (unsigned)((wrap(y0 + sy - 2, G.ny) * G.nx + wrap(x0 + sx - 2, G.nx)) * 4);
+    const int ux = x0 + idx % SX - 2, uy = y0 + idx / SX - 2;
+    int sx, sy;
+    if (WALLS && G.wall_x) {
+      sx = mirror(ux, G.nx);
+      if (ux < 0 || ux >= G.nx) walls |= 256 << (2 * k);
+    } else {
+      sx = wrap(ux, G.nx);
+    }
+    if (WALLS && G.wall_y) {
+      sy = mirror(uy, G.ny);
+      if (uy < 0 || uy >= G.ny) walls |= 512 << (2 * k);
+    } else {
+      sy = wrap(uy, G.ny);
+    }
+    stOff[k] = (unsigned)((sy * G.nx + sx) * 4);
   }
   const unsigned colT = (unsigned)(col * (int)sizeof(T)), col4 = (unsigned)(col * 4);
 
@@ -405,12 +407,19 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   };
   auto stage_store = [&](int q) {
     const int s = slot4(q);
+    int sign = walls;
+    if constexpr (WALLS) asm volatile("" : "+v"(sign));  // not one mask per staged cell across the loop
 #pragma unroll
     for (int k = 0; k < KS; ++k)
       if (k < KS - 1 || tid + k * NT < NS) {
         const float psi = st[k][1];
-        sS[s][tid + k * NT] = make_float4(st[k][0], psi_a(psi), psi_b(psi), st[k][2]);
-        sW[s][tid + k * NT] = make_float2(st[k][3], st[k][4]);
+        float wx = st[k][2], wy = st[k][3];
+        if constexpr (WALLS) {
+          wx = __uint_as_float(__float_as_uint(wx) ^ (((unsigned)sign << (23 - 2 * k)) & 0x80000000u));
+          wy = __uint_as_float(__float_as_uint(wy) ^ (((unsigned)sign << (22 - 2 * k)) & 0x80000000u));
+        }
+        sS[s][tid + k * NT] = make_float4(st[k][0], psi_a(psi), psi_b(psi), wx);
+        sW[s][tid + k * NT] = make_float2(wy, st[k][4]);
       }
   };
 
@@ -447,23 +456,45 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     __builtin_amdgcn_sched_barrier(0);
     typename Word<T>::W ldI[Q], ldR[Q];
     if (loads_q) {
-      const rsrc_t slab[3] = {buffer_of(gin + (size_t)zsrc(q - 1) * slab_bytes, slab_bytes),
-                              buffer_of(gin + (size_t)zq * slab_bytes, slab_bytes),
-                              buffer_of(gin + (size_t)zsrc(q + 1) * slab_bytes, slab_bytes)};
+      // the slabs of the three source planes, starting `early` bytes before them
+      auto slabs = [&](unsigned early, auto&& f) {
+        const rsrc_t slab[3] = {buffer_of(gin + (size_t)zsrc(q - 1) * slab_bytes - early, slab_bytes + early),
+                                buffer_of(gin + (size_t)zq * slab_bytes - early, slab_bytes + early),
+                                buffer_of(gin + (size_t)zsrc(q + 1) * slab_bytes - early, slab_bytes + early)};
+        f(slab);
+      };
       // neighbour offsets, recomputed per plane (cheaper than 18 registers across the loop)
       int ax = gx, ay = gy, arx = rgx, ary = rgy;
       asm volatile("" : "+v"(ax), "+v"(ay), "+v"(arx), "+v"(ary));
-      unsigned oI[3][3], oR[3][3];
-      column_offsets<T>(G, ax, ay, oI);
-      column_offsets<T>(G, arx, ary, oR);
-      with_mode(mode, [&](auto M) {
-        if (ringer) issue_pull<T, decltype(M)::value, LAT>(slab, pb, oR, wfR, ldR);
-        issue_pull<T, decltype(M)::value, LAT>(slab, pb, oI, wfI, ldI);
-      });
+      if (frame) {
+        int wf = walls;
+        asm volatile("" : "+v"(wf));  // keeps the corrections inside the plane loop
+        slabs((unsigned)(kMirrorSpan * pb), [&](const rsrc_t(&slab)[3]) {
+          with_mode(mode, [&](auto M) {
+            if (ringer) {
+              unsigned o[3][3];
+              column_offsets<T, true>(G, arx, ary, kMirrorSpan * pb, o);
+              issue_pull_walls<T, decltype(M)::value>(slab, pb, o, wf >> 4, ldR);
+            }
+            unsigned o[3][3];
+            column_offsets<T, true>(G, ax, ay, kMirrorSpan * pb, o);
+            issue_pull_walls<T, decltype(M)::value>(slab, pb, o, wf, ldI);
+          });
+        });
+      } else {
+        unsigned oI[3][3], oR[3][3];
+        column_offsets<T, false>(G, ax, ay, 0, oI);
+        column_offsets<T, false>(G, arx, ary, 0, oR);
+        slabs(0u, [&](const rsrc_t(&slab)[3]) {
+          with_mode(mode, [&](auto M) {
+            if (ringer) issue_pull<T, decltype(M)::value>(slab, pb, oR, ldR);
+            issue_pull<T, decltype(M)::value>(slab, pb, oI, ldI);
+          });
+        });
+      }
     }
     if constexpr (!INIT && !kStageFirst) stage_load(p + 3);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (!INIT && !kStoreLate) stage_store(p + 3);
 
     // 2. complete the pull of plane q: own cell (with deviations) and ring cell (densities).
     // The LDS bases are made opaque per pass so that the compiler does not hoist one address
@@ -484,8 +515,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
           outlet_cell<false>(A.outlet, A.pc, plane, rcol, r_rho, r_r, r_b, r_e, r_df);
         } else {
           with_mode(mode, [&](auto M) {
-            finish_pull<T, decltype(M)::value, false, SX, LAT>(ldR, S, W, bR, wfR, A.pc, r_rho, r_r, r_b, r_e, r_df,
-                                                               r_sh, r_dr);
+            finish_pull<T, decltype(M)::value, false, SX>(ldR, S, W, bR, A.pc, r_rho, r_r, r_b, r_e, r_df, r_sh, r_dr);
           });
         }
         if (is_inflow(G, rgx, rgy, zq)) {
@@ -505,8 +535,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
         nxt.shift = nxt.drho = 0.0f;
       } else {
         with_mode(mode, [&](auto M) {
-          finish_pull<T, decltype(M)::value, true, SX, LAT>(ldI, S, W, bI, wfI, A.pc, nxt.rho, nxt.rho_r, nxt.rho_b,
-                                                            nxt.e, nxt.df, nxt.shift, nxt.drho);
+          finish_pull<T, decltype(M)::value, true, SX>(ldI, S, W, bI, A.pc, nxt.rho, nxt.rho_r, nxt.rho_b, nxt.e,
+                                                       nxt.df, nxt.shift, nxt.drho);
         });
       }
       if (is_inflow(G, gx, gy, zq)) {  // R10: inflow sites are pure red at rho_r0
@@ -521,7 +551,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     // 3. the staged scalars to LDS, after the pull: planes p..p+2, which the pull reads, were
     // stored in earlier passes, and the slot written here held plane p-1, last read before the
     // previous barrier
-    if constexpr (!INIT && kStoreLate) stage_store(p + 3);
+    if constexpr (!INIT) stage_store(p + 3);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
 
@@ -549,8 +579,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
           constexpr int kCellStride = kSplitRing ? 1 : 2, kSlotStride = kSplitRing ? ND : 2 * ND;
           const int slots[3] = {sm, s0, sp};
           // beyond a lateral wall the stencil sees the boundary cell (reading R9)
-          const int xo[3] = {(wfI & 1) ? 1 : 0, 1, (wfI & 2) ? 1 : 2};
-          const int yo[3] = {(wfI & 4) ? DX : 0, DX, (wfI & 8) ? DX : 2 * DX};
+          const int xo[3] = {(walls & 1) ? 1 : 0, 1, (walls & 2) ? 1 : 2};
+          const int yo[3] = {(walls & 4) ? DX : 0, DX, (walls & 8) ? DX : 2 * DX};
 #pragma unroll
           for (int dz = 0; dz < 3; ++dz) {
 #pragma unroll
@@ -595,14 +625,14 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   if (bad) *A.unstable = 1;
 }
 
-template <typename T, int TX, int TY, bool INIT, int LAT>
+template <typename T, int TX, int TY, bool INIT, bool WALLS>
 __global__ void __launch_bounds__(TX * TY, LBM_STEP_WAVES_PER_EU) step_kernel(const StepArgs A) {
-  step_body<T, TX, TY, INIT, LAT>(A, (int)blockIdx.x, (int)gridDim.x);
+  step_body<T, TX, TY, INIT, WALLS>(A, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Many lattices in one launch: case c owns blocks [first[c], first[c+1]) of the grid, each
 // range padded to a multiple of 8 blocks so that the XCD-aware numbering holds per case.
-template <typename T, int TX, int TY, bool INIT, int LAT>
+template <typename T, int TX, int TY, bool INIT, bool WALLS>
 __global__ void __launch_bounds__(TX * TY, LBM_STEP_WAVES_PER_EU)
     batch_step_kernel(const StepArgs* __restrict__ cases, const int* __restrict__ first, int ncases) {
   const int b = (int)blockIdx.x;
@@ -614,7 +644,7 @@ __global__ void __launch_bounds__(TX * TY, LBM_STEP_WAVES_PER_EU)
     else
       hi = mid;
   }
-  step_body<T, TX, TY, INIT, LAT>(cases[lo], b - first[lo], first[lo + 1] - first[lo]);
+  step_body<T, TX, TY, INIT, WALLS>(cases[lo], b - first[lo], first[lo + 1] - first[lo]);
 }
 
 // Inflow sites (R10) after a step: each emits the red equilibrium at rho_r0 and u_in(1 + eps xi)
@@ -664,88 +694,49 @@ __global__ void __launch_bounds__(256)
 }
 
 // ================================================================== launchers
-template <typename T, int TX, int TY, int LAT>
-hipError_t launch_step_lat(const StepArgs& a, hipStream_t s) {
-  const long long blocks = (long long)tiles_in_set(a) * a.nchunks;
-  if (blocks == 0) return hipSuccess;
+template <typename T, int TX, int TY, bool WALLS>
+hipError_t launch_step_walls(const StepArgs& a, hipStream_t s) {
+  const unsigned blocks = (unsigned)((long long)a.tiles_x * a.tiles_y * a.nchunks);
   if (a.init_mode)
-    hipLaunchKernelGGL((step_kernel<T, TX, TY, true, LAT>), dim3((unsigned)blocks), dim3(TX * TY), 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, TX, TY, true, WALLS>), dim3(blocks), dim3(TX * TY), 0, s, a);
   else
-    hipLaunchKernelGGL((step_kernel<T, TX, TY, false, LAT>), dim3((unsigned)blocks), dim3(TX * TY), 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, TX, TY, false, WALLS>), dim3(blocks), dim3(TX * TY), 0, s, a);
   return hipGetLastError();
 }
 
-// Whether storage type T takes one step-kernel instance per lateral wall along the frame's
-// edges (FP16 storage) rather than one per axis (wall_tile_sets on the host side).
-template <typename T>
-constexpr bool kWallPerSide = std::is_same<T, _Float16>::value;
-
-// The step kernel with lateral free-slip walls comes in instances that reflect at the walls
-// of one axis or one wall (the frame's edges, by storage) or at all four (its corners);
-// lattices with periodic sides, and the interior tiles of a lattice with walls, keep the
-// plain pull.  Only the modes of T's tile sets are instantiated.
 template <typename T, int TX, int TY>
 hipError_t launch_step_tile(const StepArgs& a, hipStream_t s) {
-  const int mode = lat_mode_of(a.tile_set, a.geo.wall_x || a.geo.wall_y);
-  if (mode == 0) return launch_step_lat<T, TX, TY, 0>(a, s);
-  if (mode == 15) return launch_step_lat<T, TX, TY, 15>(a, s);
-  if constexpr (kWallPerSide<T>) {
-    switch (mode) {
-      case 1: return launch_step_lat<T, TX, TY, 1>(a, s);
-      case 2: return launch_step_lat<T, TX, TY, 2>(a, s);
-      case 4: return launch_step_lat<T, TX, TY, 4>(a, s);
-      case 8: return launch_step_lat<T, TX, TY, 8>(a, s);
-    }
-  } else {
-    switch (mode) {
-      case 3: return launch_step_lat<T, TX, TY, 3>(a, s);
-      case 12: return launch_step_lat<T, TX, TY, 12>(a, s);
-    }
-  }
-  return hipErrorInvalidValue;
+  return a.geo.wall_x || a.geo.wall_y ? launch_step_walls<T, TX, TY, true>(a, s)
+                                      : launch_step_walls<T, TX, TY, false>(a, s);
 }
 
-template <typename T, int TX, int TY, int LAT>
-hipError_t launch_batch_lat(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init,
-                            hipStream_t s) {
+template <typename T, int TX, int TY, bool WALLS>
+hipError_t launch_batch_walls(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init,
+                              hipStream_t s) {
   if (init)
-    hipLaunchKernelGGL((batch_step_kernel<T, TX, TY, true, LAT>), dim3((unsigned)nblocks), dim3(TX * TY), 0, s, cases,
+    hipLaunchKernelGGL((batch_step_kernel<T, TX, TY, true, WALLS>), dim3((unsigned)nblocks), dim3(TX * TY), 0, s, cases,
                        first, ncases);
   else
-    hipLaunchKernelGGL((batch_step_kernel<T, TX, TY, false, LAT>), dim3((unsigned)nblocks), dim3(TX * TY), 0, s, cases,
-                       first, ncases);
+    hipLaunchKernelGGL((batch_step_kernel<T, TX, TY, false, WALLS>), dim3((unsigned)nblocks), dim3(TX * TY), 0, s,
+                       cases, first, ncases);
   return hipGetLastError();
 }
 
 template <typename T, int TX, int TY>
-hipError_t launch_batch_tile(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init, int lat,
+hipError_t launch_batch_tile(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init, bool walls,
                              hipStream_t s) {
-  if (lat == 0) return launch_batch_lat<T, TX, TY, 0>(cases, first, ncases, nblocks, init, s);
-  if (lat == 15) return launch_batch_lat<T, TX, TY, 15>(cases, first, ncases, nblocks, init, s);
-  if constexpr (kWallPerSide<T>) {
-    switch (lat) {
-      case 1: return launch_batch_lat<T, TX, TY, 1>(cases, first, ncases, nblocks, init, s);
-      case 2: return launch_batch_lat<T, TX, TY, 2>(cases, first, ncases, nblocks, init, s);
-      case 4: return launch_batch_lat<T, TX, TY, 4>(cases, first, ncases, nblocks, init, s);
-      case 8: return launch_batch_lat<T, TX, TY, 8>(cases, first, ncases, nblocks, init, s);
-    }
-  } else {
-    switch (lat) {
-      case 3: return launch_batch_lat<T, TX, TY, 3>(cases, first, ncases, nblocks, init, s);
-      case 12: return launch_batch_lat<T, TX, TY, 12>(cases, first, ncases, nblocks, init, s);
-    }
-  }
-  return hipErrorInvalidValue;
+  return walls ? launch_batch_walls<T, TX, TY, true>(cases, first, ncases, nblocks, init, s)
+               : launch_batch_walls<T, TX, TY, false>(cases, first, ncases, nblocks, init, s);
 }
 
 template <typename T>
 hipError_t launch_batch_T(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init, int tx, int ty,
-                          int lat, hipStream_t s) {
-  if (tx == 32 && ty == 4) return launch_batch_tile<T, 32, 4>(cases, first, ncases, nblocks, init, lat, s);
-  if (tx == 32 && ty == 8) return launch_batch_tile<T, 32, 8>(cases, first, ncases, nblocks, init, lat, s);
-  if (tx == 64 && ty == 4) return launch_batch_tile<T, 64, 4>(cases, first, ncases, nblocks, init, lat, s);
-  if (tx == 64 && ty == 8) return launch_batch_tile<T, 64, 8>(cases, first, ncases, nblocks, init, lat, s);
-  if (tx == 32 && ty == 16) return launch_batch_tile<T, 32, 16>(cases, first, ncases, nblocks, init, lat, s);
+                          bool walls, hipStream_t s) {
+  if (tx == 32 && ty == 4) return launch_batch_tile<T, 32, 4>(cases, first, ncases, nblocks, init, walls, s);
+  if (tx == 32 && ty == 8) return launch_batch_tile<T, 32, 8>(cases, first, ncases, nblocks, init, walls, s);
+  if (tx == 64 && ty == 4) return launch_batch_tile<T, 64, 4>(cases, first, ncases, nblocks, init, walls, s);
+  if (tx == 64 && ty == 8) return launch_batch_tile<T, 64, 8>(cases, first, ncases, nblocks, init, walls, s);
+  if (tx == 32 && ty == 16) return launch_batch_tile<T, 32, 16>(cases, first, ncases, nblocks, init, walls, s);
   return hipErrorInvalidValue;
 }
 
@@ -794,7 +785,7 @@ int step_resident_blocks_T(int tx, int ty, int device) {
 
 #define LBM_INSTANTIATE_STEP(T)                                                 \
   template hipError_t launch_step_T<T>(const StepArgs&, int, int, hipStream_t); \
-  template hipError_t launch_batch_T<T>(const StepArgs*, const int*, int, int, bool, int, int, int, hipStream_t); \
+  template hipError_t launch_batch_T<T>(const StepArgs*, const int*, int, int, bool, int, int, bool, hipStream_t); \
   template hipError_t launch_inflow_T<T>(const StepArgs&, hipStream_t);                                         \
   template hipError_t launch_batch_inflow_T<T>(const StepArgs*, const int*, int, int, long long, hipStream_t);          \
   template int step_resident_blocks_T<T>(int, int, int);
