@@ -204,7 +204,7 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
   // depend on the tiling.
   float d_rho = Word<T>::dec_scaled(ld[0]);
   float d_t = mul_nc(t_self, d_rho);
-  if constexpr (WANT_DF) df[0] = d_rho;
+  if constexpr (WANT_DF) df[0] = SC == 1.0f ? d_rho : mul_nc(d_rho, 1.0f / SC);
   static_for<1, Q>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr Src s = resolve<i, MODE>();
@@ -230,14 +230,13 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
     }
     d_rho = add_nc(d_rho, d);
     d_t = add_nc(d_t, inc);
-    if constexpr (WANT_DF) df[i] = d;
+    // (unscaled here, not in a loop over df afterwards: that one kept both forms of the 27 values
+    // live, and the FP16 instance at 256 VGPRs instead of 208)
+    if constexpr (WANT_DF) df[i] = SC == 1.0f ? d : mul_nc(d, 1.0f / SC);
   });
   if constexpr (SC != 1.0f) {
     d_rho = mul_nc(d_rho, 1.0f / SC);
     d_t = mul_nc(d_t, 1.0f / SC);
-    if constexpr (WANT_DF)
-#pragma unroll
-      for (int i = 0; i < Q; ++i) df[i] = mul_nc(df[i], 1.0f / SC);
   }
   rho = add_nc(rho_old, d_rho);
   const float rho_t = fmaf(t_self, rho_old, d_t), rho_o = sub_nc(rho, rho_t);
@@ -311,13 +310,11 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // Density ring of time t with a 1-cell ring, 4 slots: per cell the pairs (rho_r/rho, rho)
   // (sel 0) and (rho_b/rho, rho) (sel 1), so that a reader takes its minority colour's fraction
   // and rho with one 8-byte read.  The two pairs lie in separate arrays of 4 slots each, where
-  // a wave's reads of neighbouring cells fall on distinct banks; with FP16 storage they are
-  // interleaved per cell, because the separate form makes that instance spill (measured on
-  // the jet: +1.3 % FP32, +7.6 % with lateral walls, -6 % FP16 for the separate form).
-  constexpr bool kSplitRing = !std::is_same<T, _Float16>::value;
+  // a wave's reads of neighbouring cells fall on distinct banks (against pairs interleaved per
+  // cell, on the jet: +1.3 % FP32, +5 % FP16).
   __shared__ float2 sDf[8 * ND];
   // index of pair sel of cell d in slot s
-  auto dat = [](int s, int sel, int d) { return kSplitRing ? (sel * 4 + s) * ND + d : s * 2 * ND + 2 * d + sel; };
+  auto dat = [](int s, int sel, int d) { return (sel * 4 + s) * ND + d; };
   auto slot4 = [](int q) { return q & 3; };
   // Issue order of a pass's loads (measured): with FP32 populations the staged scalars go
   // first, with 16-bit populations after the population loads.  Their LDS write waits until
@@ -576,7 +573,6 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
           asm volatile("" : "+v"(b0));
           // (a, rho) or (b, rho) of each neighbour, by the cell's minority colour
           const float2* D2 = sDf + dat(0, red_minor ? 0 : 1, 0);
-          constexpr int kCellStride = kSplitRing ? 1 : 2, kSlotStride = kSplitRing ? ND : 2 * ND;
           const int slots[3] = {sm, s0, sp};
           // beyond a lateral wall the stencil sees the boundary cell (reading R9)
           const int xo[3] = {(walls & 1) ? 1 : 0, 1, (walls & 2) ? 1 : 2};
@@ -587,7 +583,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
             for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
               for (int dx = 0; dx < 3; ++dx) {
-                const float2 v = D2[slots[dz] * kSlotStride + kCellStride * (b0 + yo[dy] + xo[dx])];
+                const float2 v = D2[slots[dz] * ND + b0 + yo[dy] + xo[dx]];
                 vp[dz][dy][dx] = v.x;
                 vr[dz][dy][dx] = v.y;
               }
