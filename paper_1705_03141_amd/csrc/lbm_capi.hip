@@ -35,7 +35,6 @@ struct lbm_ctx {
   double* diag_out = nullptr;
   int* unstable = nullptr;  // device flag the step kernel sets on a NaN / non-positive density
   int device = 0;           // the device current at lbm_create
-  long long diag_blocks = 0;
   int cur = 0;              // index of the state holding the current time
   int out_cur = 0;          // index of the outlet record of the latest time
   long long step = 0;
@@ -218,8 +217,8 @@ extern "C" lbm_status lbm_create(const lbm_params* params, void* hip_stream, lbm
     if (c->geo.face_hi == FACE_OUTFLOW)
       ok &= hipMalloc((void**)&c->outlet[k], plane * kOutletPlanes * sizeof(float)) == hipSuccess;
   }
-  c->diag_blocks = (long long)((n + 255) / 256);
-  ok = ok && hipMalloc((void**)&c->diag_part, (size_t)c->diag_blocks * 8 * sizeof(double)) == hipSuccess;
+  ok = ok && hipMalloc((void**)&c->diag_part, (size_t)scan_blocks(scan_plan(c->geo, 1)) * 8 * sizeof(double)) ==
+                 hipSuccess;
   ok = ok && hipMalloc((void**)&c->diag_out, 8 * sizeof(double)) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->unstable, sizeof(int)) == hipSuccess &&
        hipMemset(c->unstable, 0, sizeof(int)) == hipSuccess;
@@ -572,7 +571,7 @@ extern "C" lbm_status lbm_diagnostics(lbm_ctx* c, double xc, double yc, double z
   if (!c->initialised) return fail(c, LBM_ESTATE, "diagnostics before lbm_init_fields");
   AuxArgs a = aux_args(c);
   DiagQuery q{xc, yc, zc, r_in, r_out};
-  hipError_t e = launch_diag((int)c->p.storage, a, q, c->diag_part, c->diag_blocks, c->diag_out, c->stream);
+  hipError_t e = launch_diag((int)c->p.storage, a, q, c->diag_part, c->diag_out, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "diagnostics kernel");
   double h[8];
   LBM_HIP(c, hipMemcpyAsync(h, c->diag_out, sizeof(h), hipMemcpyDeviceToHost, c->stream));

@@ -102,12 +102,11 @@ hipError_t launch_coarse(int storage, const AuxArgs& a, int f, float inv_u, floa
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_diag(int storage, const AuxArgs& a, const DiagQuery& q, double* part, long long nblocks,
-                       double* out, hipStream_t s) {
+hipError_t launch_diag(int storage, const AuxArgs& a, const DiagQuery& q, double* part, double* out, hipStream_t s) {
   switch (storage) {
-    case 0: return launch_diag_T<float>(a, q, part, nblocks, out, s);
-    case 1: return launch_diag_T<_Float16>(a, q, part, nblocks, out, s);
-    case 2: return launch_diag_T<bf16>(a, q, part, nblocks, out, s);
+    case 0: return launch_diag_T<float>(a, q, part, out, s);
+    case 1: return launch_diag_T<_Float16>(a, q, part, out, s);
+    case 2: return launch_diag_T<bf16>(a, q, part, out, s);
   }
   return hipErrorInvalidValue;
 }

@@ -69,6 +69,43 @@ struct DiagQuery {
   double xc, yc, zc, r_in, r_out;
 };
 
+// A pass over the lattice that hands every cell's macroscopic state to a consumer (lbm_scan.h):
+// its split into 64 x 4 columns and z chunks, and the consumer's arguments.
+enum ScanKind { kScanCoarse = 0, kScanDiag = 1 };
+
+struct ScanArgs {
+  int tiles_x, tiles_y, zchunk, nchunks;
+  // coarse state: means over blocks of factor^3 cells, velocities times inv_u, rows of a
+  // padded box of ph x pw voxels a plane
+  int factor;
+  float inv_u;
+  float* out;
+  int ph, pw;
+  // diagnostics
+  DiagQuery q;
+  double* part;
+};
+
+inline long long scan_blocks(const ScanArgs& r) { return (long long)r.tiles_x * r.tiles_y * r.nchunks; }
+
+// The longest chunk, up to 32 planes, that still gives every place for a workgroup (4 on each of
+// 256 compute units) one; a multiple of the factor; and not so that the last chunk is the
+// outlet plane alone, whose state is formed from the plane below.
+inline ScanArgs scan_plan(const Geo& g, int factor) {
+  ScanArgs r{};
+  r.tiles_x = (g.nx + 63) / 64;
+  r.tiles_y = (g.ny + 3) / 4;
+  const long long tiles = (long long)r.tiles_x * r.tiles_y;
+  int zc = 32;
+  while (zc > factor && tiles * ((g.nz + zc - 1) / zc) < 1024) zc /= 2;
+  if (zc > g.nz) zc = g.nz;
+  if (g.face_hi == FACE_OUTFLOW)
+    while (zc == 1 || g.nz % zc == 1) ++zc;
+  r.zchunk = zc;
+  r.nchunks = (g.nz + zc - 1) / zc;
+  return r;
+}
+
 // Typed launchers, instantiated once per storage type (lbm_storage_*.hip).
 template <typename T>
 hipError_t launch_step_T(const StepArgs& a, int tx, int ty, hipStream_t s);
@@ -94,8 +131,7 @@ hipError_t launch_populations_T(const AuxArgs& a, double* out, hipStream_t s);
 template <typename T>
 hipError_t launch_coarse_T(const AuxArgs& a, int f, float inv_u, float* out, int ph, int pw, hipStream_t s);
 template <typename T>
-hipError_t launch_diag_T(const AuxArgs& a, const DiagQuery& q, double* part, long long nblocks, double* out,
-                         hipStream_t s);
+hipError_t launch_diag_T(const AuxArgs& a, const DiagQuery& q, double* part, double* out, hipStream_t s);
 
 // Dispatch on the storage code of lbm_params (0 FP32, 1 FP16, 2 BF16).
 bool step_tiling_supported(int tx, int ty);
@@ -122,7 +158,6 @@ hipError_t launch_fields(int storage, const AuxArgs& a, int x0, int y0, int z0, 
                          hipStream_t s);
 hipError_t launch_populations(int storage, const AuxArgs& a, double* out, hipStream_t s);
 hipError_t launch_coarse(int storage, const AuxArgs& a, int f, float inv_u, float* out, int ph, int pw, hipStream_t s);
-hipError_t launch_diag(int storage, const AuxArgs& a, const DiagQuery& q, double* part, long long nblocks,
-                       double* out, hipStream_t s);
+hipError_t launch_diag(int storage, const AuxArgs& a, const DiagQuery& q, double* part, double* out, hipStream_t s);
 
 }  // namespace lbm

@@ -182,7 +182,10 @@ __device__ __forceinline__ float div_nc(float a, float b) {
   return a / b;
 }
 
-template <typename T, int MODE, bool WANT_DF, int SX>
+// Complete a pull whose population loads are in ld, with the staged scalars of the three source
+// planes in S and W (row stride SX; idx0 is the cell's corner (-1, -1)).  GROUP > 0 keeps the
+// LDS reads of at most that many directions in flight, for callers with few registers.
+template <typename T, int MODE, bool WANT_DF, int SX, int GROUP = 0>
 __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], const float4* const (&S)[3], const float2* const (&W)[3],
                                             int idx0, const PullConst& C, float& rho, float& rho_r, float& rho_b,
                                             float& e_new, float (&df)[Q], float& shift_out, float& drho_out) {
@@ -233,6 +236,7 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
     // (unscaled here, not in a loop over df afterwards: that one kept both forms of the 27 values
     // live, and the FP16 instance at 256 VGPRs instead of 208)
     if constexpr (WANT_DF) df[i] = SC == 1.0f ? d : mul_nc(d, 1.0f / SC);
+    if constexpr (GROUP > 0 && i % (GROUP > 0 ? GROUP : 1) == 0) __builtin_amdgcn_sched_barrier(0);
   });
   if constexpr (SC != 1.0f) {
     d_rho = mul_nc(d_rho, 1.0f / SC);

@@ -1,7 +1,8 @@
 // lbm_storage_f32.hip -- kernels instantiated for float population storage.
-#include "lbm_step.h"
+#include "lbm_scan.h"
 
 namespace lbm {
 LBM_INSTANTIATE_STORAGE(float)
 LBM_INSTANTIATE_STEP(float)
+LBM_INSTANTIATE_SCAN(float)
 }  // namespace lbm
