@@ -3,13 +3,16 @@
 // the small element-wise operators of the encoder-decoder and its training.
 //
 // Convolution.  out[v][co] = sum_tap sum_ci in[v + off(tap)][ci] w[tap][co][ci] is a GEMM with
-// M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_ring_kernel,
-// conv_staged_kernel, wgrad_kernel) stage their operands through LDS and issue
-// v_mfma_f32_32x32x16_bf16; conv_fwd_kernel, the direct form with one wave per 32 voxels x
-// 32 output channels and v_mfma_f32_32x32x8_bf16 fed from global memory, serves channel
-// counts the others do not take (cin = 128, and planes too large for 32-bit offsets).
+// M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_ring_kernel and
+// conv_staged_kernel for activations, conv_slide_kernel for data gradients and FP32 results,
+// wgrad_kernel) stage their operands through LDS and issue v_mfma_f32_32x32x16_bf16;
+// conv_fwd_kernel, the direct form with one wave per 32 voxels x 32 output channels and
+// v_mfma_f32_32x32x8_bf16 fed from global memory, serves channel counts the others do not take
+// (cin = 128, and planes too large for 32-bit offsets).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "surrogate.h"
 
@@ -47,6 +50,18 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) w[i] = (uint32_t)f2bf(f[2 * i]) | ((uint32_t)f2bf(f[2 * i + 1]) << 16);
   return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Two values rounded to BF16 (to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  typedef float floatx2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
+}
+
+// All ones in the halves of a dword of two BF16 values that are positive.
+__device__ __forceinline__ uint32_t positive_mask(uint32_t y) {
+  return (__uint_as_float(y << 16) > 0.0f ? 0x0000FFFFu : 0u) | (__uint_as_float(y & 0xFFFF0000u) > 0.0f ? 0xFFFF0000u : 0u);
 }
 
 constexpr int kTapOff[27][3] = {
@@ -518,6 +533,271 @@ void launch_staged(const uint16_t* in, const uint16_t* w, const float* bias, uin
                      cout, relu, ntiles);
 }
 
+// ---------------------------------------------------------------- forward convolution, sliding
+// For cin in {8, 16, 32, 64}.  A block owns a co tile of 32, a tile of ROWS x SEG output columns
+// and a range of z, and sweeps the input planes of that range.  Each staged plane is used once,
+// for all the outputs it contributes to: a wave of R rows x 32 voxels keeps the accumulators of
+// three output planes (z - 1, z, z + 1) in registers, and a fragment of voxels read from LDS
+// feeds up to 9 MFMAs (3 dz x 3 dy), one of weights R.  No partial sums are exchanged between
+// waves.  What bounds it is the LDS reads beside the matrix cores: (9 + R + 2) KB per 9 R
+// v_mfma_f32_32x32x16_bf16 of 32 cycles each, 0.72 of the LDS rate at R = 2.
+//
+// The weights of the co tile stay in LDS in fragment order (1 KB per tap and 16 channels,
+// read without conflicts); the plane of voxels has a voxel stride of CP + 8 elements (4 x an odd
+// number of dwords, so that groups of 8 lanes reading 16 bytes cover all banks once).  The
+// weights are the first operand, so a lane holds 4 x 4 consecutive output channels of one voxel
+// and stores 8 bytes (16 in FP32) at a time.  The next plane's global loads are issued before the
+// MFMAs of the present one.  With 8 input channels the upper half of a 16-channel fragment is
+// zero on both sides.
+//
+// Measured, data gradient behind a ReLU mask against the kernel it replaces and its separate mask
+// pass: 32 -> 32 channels on 1x256x64x64 125 -> 93 us (of which the mask's bytes are 14), 64 -> 32
+// on 1x128x32x32 69 -> 28 us, 32 -> 64 59 -> 26 us, 64 -> 64 on 1x64x16x16 33 -> 18 us; FP32 result
+// 32 -> 32 on 1x256x64x64 98 -> 69 us.  Without its stores it takes 50 us, 1160 TFLOP/s.
+//
+// CIN: input channels; XT x WY waves, each 32 voxels x R rows; NBUF staged planes (two where they
+// fit beside the weights: one barrier per plane instead of two).
+template <int CIN_, int XT_, int WY_, int NBUF_>
+struct SlideConv {
+  static constexpr int CIN = CIN_, XT = XT_, WY = WY_, NBUF = NBUF_, R = 2;
+  static constexpr int NW = XT * WY, NT = 64 * NW;
+  static constexpr int CP = CIN < 16 ? 16 : CIN;  // channels of a staged voxel
+  static constexpr int SEG = 32 * XT, ROWS = WY * R;
+  static constexpr int RV = SEG + 2, SR = ROWS + 2;  // staged voxels per row, rows
+  static constexpr int VS = CP + 8;                  // staged voxel stride (elements)
+  static constexpr int SL = CP / 16;                 // 16-channel slices
+  static constexpr int Q = CIN / 8;                  // 16-byte chunks of a voxel in memory
+  static constexpr int PLANE = SR * RV * VS;         // elements of a staged plane
+  static constexpr int CHUNKS = SR * RV * Q;
+  static constexpr int PF = (CHUNKS + NT - 1) / NT;  // chunks per thread
+  static constexpr int WELEMS = 27 * SL * 512;       // elements of the weights' fragments
+  static constexpr int LDS = 2 * (WELEMS + NBUF * PLANE) + 128;
+  static_assert(LDS <= 163840, "tile exceeds LDS");
+};
+
+template <typename P, bool MASKED>
+__global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
+    const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
+    const uint16_t* __restrict__ relu_y, uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W,
+    int cout, int relu, int nzc, int zlen) {
+  constexpr int R = P::R, SL = P::SL, Q = P::Q;
+  __shared__ __align__(16) uint16_t sw[P::WELEMS];
+  __shared__ __align__(16) uint16_t sv[P::NBUF * P::PLANE];
+  __shared__ __align__(16) float sb[32];
+  const int t = threadIdx.x, lane = t & 63, h = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6), xt = wave % P::XT, wy = wave / P::XT;
+  const int co0 = blockIdx.y * 32;
+
+  // the blocks of one XCD (ids congruent modulo 8) take neighbouring items, which share halos
+  long long item = blockIdx.x;
+  if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
+  const int nseg = (W + P::SEG - 1) / P::SEG, nyb = (H + P::ROWS - 1) / P::ROWS;
+  const int zc = (int)(item % nzc);
+  long long col = item / nzc;
+  const int seg = (int)(col % nseg);
+  col /= nseg;
+  const int yb = (int)(col % nyb);
+  const long long nb = col / nyb;
+  const int x0 = seg * P::SEG, y0 = yb * P::ROWS, za = zc * zlen, zb = min(D, za + zlen);
+  const long long plane_elems = (long long)H * W * P::CIN;
+  const uint16_t* in_n = in + nb * D * plane_elems;
+
+  // weights and bias of the co tile
+  if constexpr (P::CIN < P::CP) {
+    for (int i = t; i < P::WELEMS / 8; i += P::NT) *reinterpret_cast<uint4*>(sw + 8 * i) = make_uint4(0, 0, 0, 0);
+    for (int i = t; i < P::NBUF * P::PLANE / 8; i += P::NT) *reinterpret_cast<uint4*>(sv + 8 * i) = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+  }
+#pragma unroll 4
+  for (int i = t; i < 27 * 32 * Q; i += P::NT) {
+    const int q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
+    *reinterpret_cast<uint4*>(sw + (tap * SL + q / 2) * 512 + ((q & 1) * 32 + co) * 8) =
+        *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
+  }
+  if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
+
+  // the staged chunks this thread moves: offset within an input plane, -1 outside of it
+  int src[P::PF], dst[P::PF];
+#pragma unroll
+  for (int k = 0; k < P::PF; ++k) {
+    const int it = t + P::NT * k, q = it % Q, v = (it / Q) % P::RV, r = it / (Q * P::RV);
+    const int ys = y0 + r - 1, x = x0 + v - 1;
+    src[k] = it < P::CHUNKS && ys >= 0 && ys < H && x >= 0 && x < W ? (ys * W + x) * P::CIN + 8 * q : -1;
+    dst[k] = (r * P::RV + v) * P::VS + 8 * q;
+  }
+  uint4 pf[P::PF];
+  auto load = [&](int p) {
+    const uint16_t* base = in_n + (long long)p * plane_elems;
+#pragma unroll
+    for (int k = 0; k < P::PF; ++k) {
+      pf[k] = make_uint4(0, 0, 0, 0);
+      if (src[k] >= 0) pf[k] = *reinterpret_cast<const uint4*>(base + src[k]);
+    }
+  };
+  auto store = [&](int p) {
+    uint16_t* d = sv + (P::NBUF == 2 ? (p & 1) * P::PLANE : 0);
+#pragma unroll
+    for (int k = 0; k < P::PF; ++k)
+      if (P::CHUNKS % P::NT == 0 || k < P::PF - 1 || t + P::NT * k < P::CHUNKS)
+        *reinterpret_cast<uint4*>(d + dst[k]) = pf[k];
+  };
+
+  floatx16 acc[3][R];  // outputs p + 1, p, p - 1 of the staged plane p
+#pragma unroll
+  for (int r = 0; r < R; ++r) acc[0][r] = acc[1][r] = acc[2][r] = floatx16{};
+
+  // every MFMA of plane p towards the output planes in MASK (bit dz: output p + 1 - dz)
+  auto plane_mfmas = [&](auto M, int p) {
+    constexpr int MASK = decltype(M)::value;
+    int b0 = (P::NBUF == 2 ? (p & 1) * P::PLANE : 0) + (wy * R * P::RV + xt * 32 + c) * P::VS + 8 * h, w0 = lane * 8;
+    asm volatile("" : "+v"(b0), "+v"(w0));
+#pragma unroll
+    for (int sl = 0; sl < SL; ++sl)
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx) {
+        uint4 wf[3][3], vf[R + 2];
+#pragma unroll
+        for (int r = 0; r < R + 2; ++r)
+          vf[r] = *reinterpret_cast<const uint4*>(sv + b0 + (r * P::RV + dx) * P::VS + sl * 16);
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+          for (int dy = 0; dy < 3; ++dy)
+            if ((MASK >> dz) & 1)
+              wf[dz][dy] = *reinterpret_cast<const uint4*>(sw + w0 + (((dz * 3 + dy) * 3 + dx) * SL + sl) * 512);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+              if ((MASK >> dz) & 1) acc[dz][r] = mfma16(wf[dz][dy], vf[r + dy], acc[dz][r]);
+      }
+  };
+
+  __syncthreads();
+  if (za > 0) load(za - 1);
+  if (za > 0) store(za - 1);
+  __syncthreads();
+#pragma unroll 1
+  for (int p = za - 1; p <= zb; ++p) {
+    const bool more = p + 1 <= zb && p + 1 < D;
+    if (more) load(p + 1);
+    // a new output plane starts from the bias: lane (h, c) holds channels 8 g + 4 h .. + 3
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        acc[0][r][4 * g + 0] = b4.x;
+        acc[0][r][4 * g + 1] = b4.y;
+        acc[0][r][4 * g + 2] = b4.z;
+        acc[0][r][4 * g + 3] = b4.w;
+      }
+    }
+    if (p >= 0 && p < D) {
+      const int mask = (p + 1 < zb ? 1 : 0) | (p >= za && p < zb ? 2 : 0) | (p > za ? 4 : 0);
+      switch (mask) {
+        case 7: plane_mfmas(std::integral_constant<int, 7>{}, p); break;
+        case 1: plane_mfmas(std::integral_constant<int, 1>{}, p); break;
+        case 2: plane_mfmas(std::integral_constant<int, 2>{}, p); break;
+        case 3: plane_mfmas(std::integral_constant<int, 3>{}, p); break;
+        case 4: plane_mfmas(std::integral_constant<int, 4>{}, p); break;
+        case 6: plane_mfmas(std::integral_constant<int, 6>{}, p); break;
+      }
+    }
+    const int x = x0 + xt * 32 + c, ya = y0 + wy * R;
+    // voxel (p - 1, ya, x), channel co0 + 4 h: output plane p - 1 is complete
+    const long long o0 = (((nb * D + p - 1) * H + ya) * (long long)W + x) * cout + co0 + 4 * h;
+    const long long orow = (long long)W * cout;
+    uint2 m[R][4];
+    if (MASKED && p > za) {  // in flight while the next plane goes to LDS
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          m[r][g] = make_uint2(0, 0);
+          if (ya + r < H && x < W) m[r][g] = *reinterpret_cast<const uint2*>(relu_y + o0 + r * orow + 8 * g);
+        }
+    }
+    if constexpr (P::NBUF == 1) __syncthreads();  // every wave is done with the plane
+    if (more) store(p + 1);
+    if (p > za) {
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (ya + r < H && x < W) {
+          const long long o = o0 + r * orow;
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            float f[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              f[k] = acc[2][r][4 * g + k];
+              if (relu) f[k] = fmaxf(f[k], 0.0f);
+            }
+            if (out_f32) {
+              *reinterpret_cast<float4*>(out_f32 + o + 8 * g) = make_float4(f[0], f[1], f[2], f[3]);
+            } else {
+              uint2 u = make_uint2(pack2(f[0], f[1]), pack2(f[2], f[3]));
+              if (MASKED) {  // the gradient of the pre-activation: 0 where the ReLU output is not positive
+                u.x &= positive_mask(m[r][g].x);
+                u.y &= positive_mask(m[r][g].y);
+              }
+              *reinterpret_cast<uint2*>(out + o + 8 * g) = u;
+            }
+          }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      acc[2][r] = acc[1][r];
+      acc[1][r] = acc[0][r];
+    }
+    __syncthreads();
+  }
+}
+
+template <typename P>
+void launch_slide(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
+                  float* out_f32, int n, int d, int h, int wd, int cout, int relu, hipStream_t s) {
+  const int ctiles = cout / 32;
+  const long long ncols = (long long)n * ((h + P::ROWS - 1) / P::ROWS) * ((wd + P::SEG - 1) / P::SEG);
+  // One block fills a compute unit's LDS: the number of z ranges that minimises the rounds of 256
+  // blocks times the planes of a block, its halo and its start-up (about 1.5 planes) included.
+  int nzc = 1;
+  double best = -1.0;
+  for (int k = 1; k <= d; ++k) {
+    const int zl = (d + k - 1) / k;
+    if ((d + zl - 1) / zl != k) continue;
+    const double cost = (double)((ncols * k * ctiles + 255) / 256) * (zl + 1.5);
+    if (best < 0.0 || cost < best) {
+      best = cost;
+      nzc = k;
+    }
+  }
+  const int zlen = (d + nzc - 1) / nzc;
+  const long long nitems = ncols * nzc;
+  const dim3 grid((unsigned)nitems, ctiles), block(P::NT);
+  if (relu_y)
+    hipLaunchKernelGGL((conv_slide_kernel<P, true>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
+                       cout, relu, nzc, zlen);
+  else
+    hipLaunchKernelGGL((conv_slide_kernel<P, false>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
+                       cout, relu, nzc, zlen);
+}
+
+// Tiles of 8 rows x 64 voxels or 16 rows x 32, whichever covers the plane with less padding.
+template <int CIN>
+void launch_slide_tile(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
+                       float* out_f32, int n, int d, int h, int wd, int cout, int relu, hipStream_t s) {
+  const long long wide = (long long)((wd + 63) / 64 * 64) * ((h + 7) / 8 * 8);
+  const long long tall = (long long)((wd + 31) / 32 * 32) * ((h + 15) / 16 * 16);
+  if (wide <= tall)
+    launch_slide<SlideConv<CIN, 2, 4, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+  else
+    launch_slide<SlideConv<CIN, 1, 8, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+}
+
 // w_t[tap'][ci][co] = w[26 - tap'][co][ci]
 __global__ void flip_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt, int cin, int cout) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -801,11 +1081,7 @@ __global__ void relu_bwd_kernel(const uint16_t* __restrict__ y, const uint16_t* 
     const uint32_t yw[4] = {yv.x, yv.y, yv.z, yv.w}, gw[4] = {gv.x, gv.y, gv.z, gv.w};
     uint32_t o[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint32_t lo = __uint_as_float(yw[k] << 16) > 0.0f ? 0x0000FFFFu : 0u;
-      const uint32_t hi = __uint_as_float(yw[k] & 0xFFFF0000u) > 0.0f ? 0xFFFF0000u : 0u;
-      o[k] = gw[k] & (lo | hi);
-    }
+    for (int k = 0; k < 4; ++k) o[k] = gw[k] & positive_mask(yw[k]);
     *reinterpret_cast<uint4*>(dx + e) = make_uint4(o[0], o[1], o[2], o[3]);
   } else {
     for (long long j = e; j < count && j < e + 8; ++j) dx[j] = bf2f(y[j]) > 0.0f ? dy[j] : (uint16_t)0;
@@ -1029,43 +1305,63 @@ inline int done() { return hipGetLastError() == hipSuccess ? 0 : -2; }
 }  // namespace
 
 namespace {
-int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32, int n, int d,
-                  int h, int wd, int cin, int cout, int relu, void* stream) {
+// grad: a data gradient; relu_y: the result is 0 where it is not positive (BF16 output)
+int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
+                  float* out_f32, int n, int d, int h, int wd, int cin, int cout, int relu, bool grad, void* stream) {
   if (n < 1 || d < 1 || h < 1 || wd < 1 || cin < 8 || cin % 8 || cout < 32 || cout % 32 || !in || !w ||
       (!out && !out_f32))
     return -1;
   const long long nvox = (long long)n * d * h * wd;
-  const bool small_plane = (long long)h * wd * cin < (1LL << 31);
+  hipStream_t s = S(stream);
+  const bool small_plane = (long long)h * wd * cin < (1LL << 31);  // 32-bit offsets within an input plane
+  // The sliding kernel takes gradients and FP32 results (up to 2.5 times as fast as the ring and
+  // staged kernels, measured below), and moves 16 bytes at a time.  BF16 activations keep those
+  // kernels: another order of the sums moves one in 10^4 of them by a BF16 ulp, which the
+  // network carries to 5e-4 of its prediction (measured), and predictions stay reproducible bit
+  // for bit.
+  const bool slide = (out_f32 || grad) && small_plane && aligned16(in) && aligned16(w) &&
+                     (out_f32 ? aligned16(out_f32) : ((uintptr_t)out & 7) == 0) && ((uintptr_t)relu_y & 7) == 0;
+  if (slide && cin <= 64) {
+    switch (cin) {
+      case 8: launch_slide_tile<8>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
+      case 16: launch_slide_tile<16>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
+      case 32: launch_slide_tile<32>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
+      case 64:
+        launch_slide<SlideConv<64, 1, 4, 1>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+        return done();
+    }
+  }
   switch (cin) {
     case 8:
       if (small_plane)
-        launch_ring<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream));
+        launch_ring<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
-        launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, S(stream));
+        launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s);
       break;
     case 16:
       if (small_plane)
-        launch_ring<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream));
+        launch_ring<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
-        launch_staged<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream));
+        launch_staged<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       break;
     case 32:
       if (small_plane)
-        launch_ring<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream));
+        launch_ring<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
-        launch_staged<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream));
+        launch_staged<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       break;
-    case 64: launch_staged<64>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, S(stream)); break;
-    case 128: launch_conv<128>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, S(stream)); break;
+    case 64: launch_staged<64>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s); break;
+    case 128: launch_conv<128>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s); break;
     default: return -1;
   }
-  return done();
+  const int rc = done();
+  return rc != 0 || !relu_y ? rc : surr_relu_bwd(relu_y, out, out, nvox * cout, stream);
 }
 }  // namespace
 
 extern "C" int surr_conv3d_fwd(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32,
                                int n, int d, int h, int wd, int cin, int cout, int relu, void* stream) {
-  return conv_dispatch(in, w, bias, out, out_f32, n, d, h, wd, cin, cout, relu, stream);
+  return conv_dispatch(in, w, bias, nullptr, out, out_f32, n, d, h, wd, cin, cout, relu, false, stream);
 }
 
 extern "C" int surr_conv3d_flip_weights(const uint16_t* w, uint16_t* w_t, int cin, int cout, void* stream) {
@@ -1077,12 +1373,9 @@ extern "C" int surr_conv3d_flip_weights(const uint16_t* w, uint16_t* w_t, int ci
 
 extern "C" int surr_conv3d_dgrad(const uint16_t* dout, const uint16_t* w_t, const uint16_t* relu_y, uint16_t* din, int n,
                                  int d, int h, int wd, int cin, int cout, void* stream) {
-  // the forward convolution of dout (cout channels) with w_t gives din (cin channels); the
-  // ReLU mask is a pass of its own (the convolution kernels have no registers to spare for it)
+  // the forward convolution of dout (cout channels) with w_t gives din (cin channels)
   if (!din) return -1;
-  const int rc = conv_dispatch(dout, w_t, nullptr, din, nullptr, n, d, h, wd, cout, cin, 0, stream);
-  if (rc != 0 || !relu_y) return rc;
-  return surr_relu_bwd(relu_y, din, din, (long long)n * d * h * wd * cin, stream);
+  return conv_dispatch(dout, w_t, nullptr, relu_y, din, nullptr, n, d, h, wd, cout, cin, 0, true, stream);
 }
 
 extern "C" size_t surr_conv3d_wgrad_scratch_bytes(int n, int d, int h, int wd, int cin, int cout) {
