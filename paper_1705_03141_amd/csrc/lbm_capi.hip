@@ -40,6 +40,7 @@ struct lbm_ctx {
   long long step = 0;
   bool initialised = false;
   int tx = 0, ty = 0, zchunk = 0;  // 0: chosen at the first step (choose_tiling, auto_zchunk)
+  bool bricks = false;             // stepped by bricks (chosen at the first step, like tx and ty)
   bool in_batch = false;           // advanced only by lbm_batch_step
   bool frozen = false;             // a batch case found unstable: no longer stepped
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -274,6 +275,7 @@ extern "C" lbm_status lbm_set_tiling(lbm_ctx* c, int tx, int ty, int zchunk) {
   c->tx = tx;
   c->ty = ty;
   c->zchunk = zchunk;
+  c->bricks = false;
   return LBM_OK;
 }
 
@@ -320,14 +322,15 @@ extern "C" lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_r, const dou
   return LBM_OK;
 }
 
-// Planes per workgroup when none is set: the number of z chunks that minimises
-// (rounds of resident workgroups) x (planes per chunk + the 2 planes each chunk pulls first).
-static int zchunk_for(const lbm_ctx* c, long long tiles) {
+// Planes per workgroup of tx x ty tiles when none is set: the number of z chunks that minimises
+// (rounds of resident workgroups) x (planes per chunk + the 2 planes each chunk pulls first);
+// *cost is that product.
+static int auto_zchunk(const lbm_ctx* c, int tx, int ty, long long* cost = nullptr) {
   const Geo& G = c->geo;
-  if (tiles < 1) return G.nz;
+  const long long tiles = (long long)((G.nx + tx - 1) / tx) * ((G.ny + ty - 1) / ty);
   int dev = 0;
   (void)hipGetDevice(&dev);
-  long long resident = step_resident_blocks((int)c->p.storage, c->tx, c->ty, dev);
+  long long resident = step_resident_blocks((int)c->p.storage, tx, ty, dev);
   if (resident < 1) resident = 1024;
   long long best_cost = -1;
   int best = G.nz;
@@ -335,29 +338,30 @@ static int zchunk_for(const lbm_ctx* c, long long tiles) {
     const int zc = (G.nz + nch - 1) / nch;
     if ((G.nz + zc - 1) / zc != nch) continue;  // same chunking as a smaller count
     const long long rounds = (tiles * nch + resident - 1) / resident;
-    const long long cost = rounds * (zc + 2);
-    if (best_cost < 0 || cost < best_cost) {
-      best_cost = cost;
+    const long long k = rounds * (zc + 2);
+    if (best_cost < 0 || k < best_cost) {
+      best_cost = k;
       best = zc;
     }
   }
+  if (cost) *cost = best_cost;
   return best;
 }
 
-static int auto_zchunk(const lbm_ctx* c) {
-  const Geo& G = c->geo;
-  return zchunk_for(c, (long long)((G.nx + c->tx - 1) / c->tx) * ((G.ny + c->ty - 1) / c->ty));
-}
+// Lattices of at most this many cells for which no tile shape has been set are stepped by bricks
+// (lbm_brick.h): faster up to 48^3 at least, slower from 64^3.
+static constexpr long long kBrickCells = 1ll << 17;
 
 static void choose_tiling(lbm_ctx* c) {
   if (c->tx == 0) {
+    c->bricks = c->geo.n <= kBrickCells;
     // measured on MI355X: 64 x 4 tiles on rows of 64 cells or more, 32 x 8 otherwise
     // (lbm_autotune times the shapes for a given lattice)
     const bool wide = c->geo.nx >= 64;
     c->tx = wide ? 64 : 32;
     c->ty = wide ? 4 : 8;
   }
-  if (c->zchunk < 1) c->zchunk = auto_zchunk(c);
+  if (c->zchunk < 1) c->zchunk = auto_zchunk(c, c->tx, c->ty);
 }
 
 // Arguments of the step kernel for the state of parity cur (outlet record out_cur).
@@ -418,7 +422,8 @@ static lbm_status enqueue_one(lbm_ctx* c) {
   StepArgs s{};
   choose_tiling(c);
   fill_step_args(c, c->cur, c->out_cur, s);
-  hipError_t e = launch_step((int)c->p.storage, s, c->tx, c->ty, c->stream);
+  hipError_t e = c->bricks ? launch_bricks((int)c->p.storage, s, c->stream)
+                           : launch_step((int)c->p.storage, s, c->tx, c->ty, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "step kernel");
   if (G.inflow) {
     e = launch_inflow((int)c->p.storage, s, c->stream);
@@ -795,7 +800,7 @@ static void batch_tiling(lbm_batch* b) {
     resident = std::max<long long>(resident, step_resident_blocks((int)c->p.storage, c->tx, c->ty, dev));
   }
   for (lbm_ctx* c : b->c)
-    if (c->zchunk < 1) c->zchunk = columns >= resident ? std::min(c->geo.nz, kBatchChunk) : auto_zchunk(c);
+    if (c->zchunk < 1) c->zchunk = columns >= resident ? std::min(c->geo.nz, kBatchChunk) : auto_zchunk(c, c->tx, c->ty);
 }
 
 static lbm_status build_groups(lbm_batch* b) {
@@ -1005,8 +1010,9 @@ extern "C" double lbm_batch_last_step_ms(const lbm_batch* cb) {
 // Time every supported tile shape on a scratch lattice with the parameters of c (blue fluid
 // at rest) for trial_steps steps each, on `stream`, and return the fastest in (tx, ty).  c's
 // own state is not touched.
+// bricks, if given: whether stepping by bricks was faster still (lattices of at most kBrickCells).
 static lbm_status time_tile_shapes(const lbm_ctx* c, void* stream, int trial_steps, int& tx, int& ty,
-                                   std::string& err) {
+                                   std::string& err, bool* bricks = nullptr) {
   static const int shapes[][2] = {{32, 8}, {64, 4}, {32, 4}};
   lbm_ctx* t = nullptr;
   lbm_status st = lbm_create(&c->p, stream, &t);
@@ -1037,6 +1043,16 @@ static lbm_status time_tile_shapes(const lbm_ctx* c, void* stream, int trial_ste
       ty = sh[1];
     }
   }
+  if (bricks) {
+    *bricks = false;
+    if (st == LBM_OK && c->geo.n <= kBrickCells) {
+      t->bricks = true;
+      if ((st = lbm_step(t, 1)) == LBM_OK && (st = lbm_step(t, trial_steps)) == LBM_OK) {
+        const double ms = lbm_last_step_kernel_ms(t);
+        *bricks = ms > 0.0 && ms < best;
+      }
+    }
+  }
   err = t->err;
   lbm_destroy(t);
   return st;
@@ -1047,10 +1063,12 @@ extern "C" lbm_status lbm_autotune(lbm_ctx* c, int trial_steps) {
   if (trial_steps < 1) return fail(c, LBM_EINVAL, "trial_steps must be >= 1");
   int tx = 0, ty = 0;
   std::string err;
-  const lbm_status st = time_tile_shapes(c, c->stream, trial_steps, tx, ty, err);
+  bool bricks = false;
+  const lbm_status st = time_tile_shapes(c, c->stream, trial_steps, tx, ty, err, &bricks);
   if (st != LBM_OK) return fail(c, st, "autotune: " + err);
   c->tx = tx;
   c->ty = ty;
+  c->bricks = bricks;
   c->zchunk = 0;
   return LBM_OK;
 }

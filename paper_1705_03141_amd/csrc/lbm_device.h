@@ -77,9 +77,15 @@ struct Geo {
   unsigned long long seed;   // noise seed
 };
 
+// v modulo n.  Positions are rarely more than one lattice away, so the division (some 40
+// instructions) is left to the lanes that need it.
 __device__ __forceinline__ int wrap(int v, int n) {
-  v = v % n;
-  return v < 0 ? v + n : v;
+  v = v < 0 ? v + n : (v >= n ? v - n : v);
+  if ((unsigned)v >= (unsigned)n) {
+    v = v % n;
+    v = v < 0 ? v + n : v;
+  }
+  return v;
 }
 
 // The cell a position beyond the walls of an axis of n cells mirrors to (half a cell outside the

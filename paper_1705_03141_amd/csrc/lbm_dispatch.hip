@@ -17,6 +17,15 @@ hipError_t launch_step(int storage, const StepArgs& a, int tx, int ty, hipStream
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_bricks(int storage, const StepArgs& a, hipStream_t s) {
+  switch (storage) {
+    case 0: return launch_bricks_T<float>(a, s);
+    case 1: return launch_bricks_T<_Float16>(a, s);
+    case 2: return launch_bricks_T<bf16>(a, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_batch(int storage, const StepArgs* cases, const int* first, int ncases, int nblocks, bool init,
                         int tx, int ty, bool walls, hipStream_t s) {
   switch (storage) {

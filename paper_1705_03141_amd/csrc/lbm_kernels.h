@@ -110,6 +110,8 @@ inline ScanArgs scan_plan(const Geo& g, int factor) {
 template <typename T>
 hipError_t launch_step_T(const StepArgs& a, int tx, int ty, hipStream_t s);
 template <typename T>
+hipError_t launch_bricks_T(const StepArgs& a, hipStream_t s);
+template <typename T>
 hipError_t launch_inflow_T(const StepArgs& a, hipStream_t s);
 template <typename T>
 hipError_t launch_batch_T(const StepArgs* cases, const int* first, int ncases, int nblocks, bool init, int tx, int ty,
@@ -136,6 +138,8 @@ hipError_t launch_diag_T(const AuxArgs& a, const DiagQuery& q, double* part, dou
 // Dispatch on the storage code of lbm_params (0 FP32, 1 FP16, 2 BF16).
 bool step_tiling_supported(int tx, int ty);
 hipError_t launch_step(int storage, const StepArgs& a, int tx, int ty, hipStream_t s);
+// The step of a small lattice by bricks (lbm_brick.h); its tile shape and z chunk are not used.
+hipError_t launch_bricks(int storage, const StepArgs& a, hipStream_t s);
 // One step of several lattices in one launch: cases (device array of ncases argument blocks,
 // all with the same storage, tile shape and lateral rule: walls = free-slip x or y walls),
 // first (device, ncases + 1 block offsets, each a multiple of 8), nblocks = first[ncases].

@@ -142,6 +142,23 @@ __device__ __forceinline__ void issue_pull(const rsrc_t (&slab)[3], int plane_by
 // scalar offset is added.
 constexpr int kMirrorSpan = 6;
 
+// Byte correction of a lane's offset for population J pulled from source offset (DX, DY):
+// at[axis][side] is all ones where the cell lies on that wall (axis 0: x, 1: y; side 0: low).
+template <int J, int DX, int DY>
+__device__ __forceinline__ unsigned mirror_shift(const unsigned (&at)[2][2], int plane_bytes) {
+  constexpr int jx = mirror_x(J), jy = mirror_y(J), jxy = mirror_x(jy);
+  static_assert(jx - J <= kMirrorSpan && J - jx <= kMirrorSpan && jy - J <= kMirrorSpan && J - jy <= kMirrorSpan &&
+                    jxy - J <= kMirrorSpan && J - jxy <= kMirrorSpan,
+                "mirrored population further than the descriptors reach");
+  const unsigned mx = DX == 0 ? 0u : at[0][DX > 0], my = DY == 0 ? 0u : at[1][DY > 0];
+  unsigned v = 0;
+  if constexpr (DX != 0) v += mx & (unsigned)((jx - J) * plane_bytes);
+  if constexpr (DY != 0) v += my & (unsigned)((jy - J) * plane_bytes);
+  // at a corner both mirror: the two differences do not simply add
+  if constexpr (DX != 0 && DY != 0 && jxy - jx - jy + J != 0) v += (mx & my) & (unsigned)((jxy - jx - jy + J) * plane_bytes);
+  return v;
+}
+
 template <typename T, int MODE>
 __device__ __forceinline__ void issue_pull_walls(const rsrc_t (&slab)[3], int plane_bytes, const unsigned (&o)[3][3],
                                                  int wf, typename Word<T>::W (&ld)[Q]) {
@@ -149,17 +166,7 @@ __device__ __forceinline__ void issue_pull_walls(const rsrc_t (&slab)[3], int pl
   static_for<0, Q>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr Src s = resolve<i, MODE>();
-    constexpr int jx = mirror_x(s.j), jy = mirror_y(s.j), jxy = mirror_x(jy);
-    static_assert(jx - s.j <= kMirrorSpan && s.j - jx <= kMirrorSpan && jy - s.j <= kMirrorSpan &&
-                      s.j - jy <= kMirrorSpan && jxy - s.j <= kMirrorSpan && s.j - jxy <= kMirrorSpan,
-                  "mirrored population further than the descriptors reach");
-    unsigned v = o[s.dy + 1][s.dx + 1];
-    const unsigned mx = s.dx == 0 ? 0u : at[0][s.dx > 0], my = s.dy == 0 ? 0u : at[1][s.dy > 0];
-    if constexpr (s.dx != 0) v += mx & (unsigned)((jx - s.j) * plane_bytes);
-    if constexpr (s.dy != 0) v += my & (unsigned)((jy - s.j) * plane_bytes);
-    // at a corner both mirror: the two differences do not simply add
-    if constexpr (s.dx != 0 && s.dy != 0 && jxy - jx - jy + s.j != 0)
-      v += (mx & my) & (unsigned)((jxy - jx - jy + s.j) * plane_bytes);
+    const unsigned v = o[s.dy + 1][s.dx + 1] + mirror_shift<s.j, s.dx, s.dy>(at, plane_bytes);
     ld[i] = Word<T>::load(slab[s.dz + 1], v, s.j * plane_bytes);
   });
 }
@@ -397,8 +404,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   auto zsrc = [&](int q) { return zper ? wrap(q, G.nz) : min(max(q, 0), G.nz - 1); };
   auto needs_pull = [&](int q) { return zper || (q >= 0 && q < G.nz); };
 
-  float st[KS][5];
-  auto stage_load = [&](int q) {
+  auto stage_load = [&](int q, float(&st)[KS][5]) {
     const rsrc_t r = buffer_of(A.sc_in + (size_t)zsrc(q) * 5 * (size_t)plane, sc_bytes);
 #pragma unroll
     for (int k = 0; k < KS; ++k)
@@ -406,7 +412,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
 #pragma unroll
         for (int c = 0; c < 5; ++c) st[k][c] = load_f32(r, stOff[k], c * plane * 4);
   };
-  auto stage_store = [&](int q) {
+  auto stage_store = [&](int q, const float(&st)[KS][5]) {
     const int s = slot4(q);
     int sign = walls;
     if constexpr (WALLS) asm volatile("" : "+v"(sign));  // not one mask per staged cell across the loop
@@ -430,12 +436,11 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   bool bad = false;  // a collided cell had a NaN, infinite or non-positive density
 
   if constexpr (!INIT) {
-    stage_load(z0 - 2);
-    stage_store(z0 - 2);
-    stage_load(z0 - 1);
-    stage_store(z0 - 1);
-    stage_load(z0);
-    stage_store(z0);
+    float st[3][KS][5];  // the first three planes in one go
+#pragma unroll
+    for (int k = 0; k < 3; ++k) stage_load(z0 - 2 + k, st[k]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) stage_store(z0 - 2 + k, st[k]);
   }
   __syncthreads();
 
@@ -453,7 +458,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     // that its loads go out, and the barrier is reached, sooner.
     __builtin_amdgcn_s_setprio(1);
     // 1. the loads of the scalars of plane p+3 and of the populations of plane p+1
-    if constexpr (!INIT && kStageFirst) stage_load(p + 3);
+    float st[KS][5];
+    if constexpr (!INIT && kStageFirst) stage_load(p + 3, st);
     __builtin_amdgcn_sched_barrier(0);
     typename Word<T>::W ldI[Q], ldR[Q];
     if (loads_q) {
@@ -494,7 +500,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
         });
       }
     }
-    if constexpr (!INIT && !kStageFirst) stage_load(p + 3);
+    if constexpr (!INIT && !kStageFirst) stage_load(p + 3, st);
     __builtin_amdgcn_sched_barrier(0);
 
     // 2. complete the pull of plane q: own cell (with deviations) and ring cell (densities).
@@ -552,7 +558,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     // 3. the staged scalars to LDS, after the pull: planes p..p+2, which the pull reads, were
     // stored in earlier passes, and the slot written here held plane p-1, last read before the
     // previous barrier
-    if constexpr (!INIT) stage_store(p + 3);
+    if constexpr (!INIT) stage_store(p + 3, st);
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
 
