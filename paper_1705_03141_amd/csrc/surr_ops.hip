@@ -608,11 +608,19 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
     for (int i = t; i < P::NBUF * P::PLANE / 8; i += P::NT) *reinterpret_cast<uint4*>(sv + 8 * i) = make_uint4(0, 0, 0, 0);
     __syncthreads();
   }
-#pragma unroll 4
-  for (int i = t; i < 27 * 32 * Q; i += P::NT) {
-    const int q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
-    *reinterpret_cast<uint4*>(sw + (tap * SL + q / 2) * 512 + ((q & 1) * 32 + co) * 8) =
-        *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
+  {
+    constexpr int WCH = 27 * 32 * Q, WPT = (WCH + P::NT - 1) / P::NT;
+    uint4 wr[WPT];
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
+      wr[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
+    }
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
+      *reinterpret_cast<uint4*>(sw + (tap * SL + q / 2) * 512 + ((q & 1) * 32 + co) * 8) = wr[k];
+    }
   }
   if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
 
@@ -811,220 +819,298 @@ __global__ void flip_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict
 
 // ---------------------------------------------------------------- weight gradient
 // dw[tap][co][ci] = sum_v dout[v][co] in[v + off(tap)][ci]: per tap a GEMM with M = cout,
-// N = cin, K = voxels.  The voxels are walked as row segments of kSeg along x, ordered
-// (n, z, segment, y) with y fastest; block (c, tile) of three waves owns the (co, ci) tile of
-// 32 x 32 and the c-th of nchunks contiguous ranges of row segments.  Wave k accumulates
-// the nine taps with dz = k - 1.  Per segment the block stages dout^T [co][x] into LDS, and
-// wave k stages the source rows (z + dz, y') as in^T [ci][x] over x0 - 4 .. x0 + kSeg + 3;
-// the three rows y - 1, y, y + 1 live in a ring, so the next segment of the same column
-// stages only row y + 2.  The K order of an MFMA is free: with v_mfma_f32_32x32x16_bf16 lane
-// half h takes voxels x0 + 32 h + 8 s + j at step s, so each lane walks its 32 voxels eight
-// at a time and the dx = -1, +1 operands are its aligned 16-byte words shifted by one
-// element, the word before or after coming from the previous or the next step.
-constexpr int kSeg = 64;            // voxels per row segment
-constexpr int kRsA = kSeg + 8;      // LDS row stride of dout^T (elements; 36 dwords)
-constexpr int kRowB = kSeg + 16;    // staged source row, x0 - 8 .. x0 + kSeg + 7
-constexpr int kRsB = kRowB + 8;     // LDS row stride of in^T (44 dwords)
-// Channel row r of a staged tile starts at r * stride + (r / 8) * 16 elements: the 8-dword
-// shift per group of 8 rows spreads the transposing 2-byte stores of the four 8-channel
-// groups over distinct banks (stride * 8 is a multiple of 32 dwords); 16-byte reads along x
-// keep their conflict-free pattern.
-__host__ __device__ constexpr int trow(int r, int stride) { return r * stride + (r >> 3) * 16; }
-constexpr int kTileA = 32 * kRsA + 4 * 16;  // elements of a staged dout^T tile
-constexpr int kTileB = 32 * kRsB + 4 * 16;  // elements of a staged in^T row
-constexpr int kWgradBlocks = 512;   // two resident blocks (LDS-bound) on each of 256 compute units
-
-__host__ __device__ inline int nseg_of(int W) { return (W + kSeg - 1) / kSeg; }
+// N = cin, K = voxels.  A block of eight waves owns a 32 x 32 (co, ci) tile and walks, along z, tiles
+// of 16 rows x 32 voxels of `in`: per step one plane z of `in` (with the voxels left and right of
+// it) and the planes z - 1, z, z + 1 of dout (with a row above and below; a ring of three, so a
+// step stages one) lie in LDS as they lie in memory, and are read with ds_read_b64_tr_b16, which
+// transposes 4 voxels x 16 channels on the way to registers: lane l gets 4 voxels of channel l % 16
+// of its group, so two reads make an MFMA operand and a shift in x is a shift of the address.
+//
+// An operand of `in` (a row, a shift dx, 16 voxels) meets the 9 rows (z - dz, y - dy) of dout, and an
+// operand of dout stays in registers for the three rows of `in` it meets while y advances.  The 27
+// taps are split over four waves so that each keeps 7 accumulators (112 registers) and shares
+// operands: wave dx of the first three takes 7 of the 9 (dz, dy), the fourth the other two for
+// every dx, and the bias (dout against ones).  Two such groups take 8 rows each.  Per 7 MFMAs of
+// 32 cycles a wave reads 4 KB of LDS, 0.6 of its rate over the block.
+//
+// With 8 input channels (PACK8) one MFMA takes all three dx: rows of voxels are 16 bytes apart, so
+// 32 consecutive elements of a row are the channels of the voxels x - 1, x, x + 1 (and one unused),
+// and each wave keeps all 9 (dz, dy) for its rows.
+//
+// One block per compute unit: 256 partial sums in all, a third of the time of a full-resolution
+// layer at 512.  The next step's planes are loaded during the present one's MFMAs.  Measured
+// (with the sum of the partials), 32 -> 32 channels on 1x256x64x64: WGRADFIG
+constexpr int kWgX = 32, kWgY = 16;               // voxels and rows of a tile
+constexpr int kWgThreads = 512, kWgBlocks = 256;  // one resident block on each of 256 compute units
+constexpr int kWgRow = kWgX * 32, kWgPlane = (kWgY + 2) * kWgRow;  // elements of a staged dout row, plane
 
 struct WgradPlan {
-  long long nsr;  // row segments
+  long long steps;  // (column, plane) pairs
+  int nxb, nyb;     // tiles of a plane
   int nchunks, ci_tiles, tiles;
 };
 
 inline WgradPlan wgrad_plan(int n, int d, int h, int wd, int cin, int cout) {
   WgradPlan p;
-  p.nsr = (long long)n * d * h * nseg_of(wd);
+  p.nxb = (wd + kWgX - 1) / kWgX;
+  p.nyb = (h + kWgY - 1) / kWgY;
+  p.steps = (long long)n * p.nyb * p.nxb * d;
   p.ci_tiles = (cin + 31) / 32;
   p.tiles = (cout / 32) * p.ci_tiles;
-  const long long want = (kWgradBlocks + p.tiles - 1) / p.tiles;
-  p.nchunks = (int)(want < p.nsr ? want : p.nsr);
-  if (p.nchunks < 1) p.nchunks = 1;
+  const long long want = (kWgBlocks + p.tiles - 1) / p.tiles;
+  p.nchunks = (int)(want < p.steps ? want : p.steps);
   return p;
 }
 
-// [p.e7, c.e0 .. c.e6] and [c.e1 .. c.e7, n.e0] of 8-element BF16 words (element 2i in the
-// low half of dword i)
-__device__ __forceinline__ uint4 shift_in_prev(uint4 p, uint4 c) {
-  return make_uint4((c.x << 16) | (p.w >> 16), (c.y << 16) | (c.x >> 16), (c.z << 16) | (c.y >> 16),
-                    (c.w << 16) | (c.z >> 16));
-}
-__device__ __forceinline__ uint4 shift_in_next(uint4 c, uint4 n) {
-  return make_uint4((c.x >> 16) | (c.y << 16), (c.y >> 16) | (c.z << 16), (c.z >> 16) | (c.w << 16),
-                    (c.w >> 16) | (n.x << 16));
+// Two transposing reads: the operand of 16 voxels x 32 channels that begins at `p` + this lane's
+// offset, rows of voxels `stride` elements apart.
+__device__ __forceinline__ uint4 read_tr(const uint16_t* p, int stride) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * stride));
+  const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+  return make_uint4(a.x, a.y, b.x, b.y);
 }
 
-__global__ void __launch_bounds__(192, 2) wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dout,
-                                                       float* __restrict__ part, float* __restrict__ bpart, int D, int H,
-                                                       int W, int cin, int cout, long long nsr, int nchunks,
-                                                       int ci_tiles) {
-  __shared__ __align__(16) uint16_t sA[kTileA];
-  __shared__ __align__(16) uint16_t sB[3][3][kTileB];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, dz = wave - 1;
+template <bool PACK8>
+__global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ dout,
+                                                              float* __restrict__ part, float* __restrict__ bpart, int D, int H,
+                                                              int W, int cin, int cout, WgradPlan P) {
+  constexpr int IC = PACK8 ? 8 : 32;                // channels of a staged voxel of `in`
+  constexpr int IRV = PACK8 ? kWgX + 4 : kWgX + 2;  // staged voxels of a row of `in`
+  constexpr int NACC = PACK8 ? 9 : 7;
+  constexpr int IN0 = 3 * kWgPlane;                 // where `in` begins
+  constexpr int STAGE = IN0 + kWgY * IRV * IC, REDUCE = 4 * NACC * 2048;
+  __shared__ __align__(16) uint16_t lds[STAGE > REDUCE ? STAGE : REDUCE];
+  const int t = threadIdx.x, lane = t & 63, h = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int chunk = blockIdx.x;
-  const int co0 = (blockIdx.y / ci_tiles) * 32, ci0 = (blockIdx.y % ci_tiles) * 32;
-  const long long r0 = nsr * chunk / nchunks, r1 = nsr * (chunk + 1) / nchunks;
-  const int nseg = nseg_of(W);
+  const int co0 = (blockIdx.y / P.ci_tiles) * 32, ci0 = (blockIdx.y % P.ci_tiles) * 32;
+  const long long p0 = P.steps * chunk / P.nchunks, p1 = P.steps * (chunk + 1) / P.nchunks;
   const bool do_bias = bpart != nullptr && ci0 == 0;
+  // lane offsets of the transposing reads: voxel 8 h + (l % 16) / 4, channel 16 (l / 16 % 2) + 4 (l % 4)
+  const int vox = 8 * h + ((lane & 15) >> 2), chan = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const int offA = vox * 32 + chan, offB = vox * IC + chan;
 
-  floatx16 acc[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) acc[k] = floatx16{};
-  float bsum = 0.0f;  // wave 0, lane (h, c): channel co0 + c over voxels x0 + 32 h .. + 31
+  const uint4 ones = make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
 
-  // 16-byte chunks this thread moves, two voxels at a time so that the transposed stores are
-  // whole dwords (one channel of both voxels, paired by v_perm): dout^T item it = t
-  // (it < 128) -> voxels x0 + 2 (it / 4) + {0, 1}, channels co0 + 8 (it % 4) ..; in^T item
-  // lane + 64 k -> voxels x0 - 8 + 2 ((lane + 64 k) / 4) + {0, 1}, channels ci0 + 8 ((lane + 64 k) % 4) ..
-  constexpr int PB = (2 * kRowB + 63) / 64;  // voxel-pair items per lane of a source row
-  auto pair_store = [&](uint16_t* base, int stride, int q, int xi, const uint4& A, const uint4& B) {
-    const uint32_t a4[4] = {A.x, A.y, A.z, A.w}, b4[4] = {B.x, B.y, B.z, B.w};
+  // the chunks of 16 bytes this thread moves per plane
+  constexpr int DCH = (kWgY + 2) * kWgX * 4, ICH = kWgY * IRV * (IC / 8);
+  constexpr int DPF = (DCH + kWgThreads - 1) / kWgThreads, IPF = (ICH + kWgThreads - 1) / kWgThreads;
+  uint4 pd[DPF], pi[IPF];
+  auto load_dout = [&](long long nb, int z, int y0, int x0) {
+    const uint16_t* base = dout + (nb * D + z) * H * (long long)W * cout + co0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      *reinterpret_cast<uint32_t*>(base + trow(8 * q + 2 * k, stride) + xi) = __builtin_amdgcn_perm(b4[k], a4[k], 0x05040100u);
-      *reinterpret_cast<uint32_t*>(base + trow(8 * q + 2 * k + 1, stride) + xi) =
-          __builtin_amdgcn_perm(b4[k], a4[k], 0x07060302u);
+    for (int k = 0; k < DPF; ++k) {
+      int it = t + kWgThreads * k;
+      asm volatile("" : "+v"(it));  // the addresses are formed per step, not kept
+      const int q = it & 3, v = (it >> 2) % kWgX, r = (it >> 2) / kWgX;
+      const int y = y0 + r - 1, x = x0 + v;
+      pd[k] = make_uint4(0, 0, 0, 0);
+      if (it < DCH && z >= 0 && z < D && y >= 0 && y < H && x < W)
+        pd[k] = *reinterpret_cast<const uint4*>(base + ((long long)y * W + x) * cout + 8 * q);
     }
   };
-  auto load_dout = [&](long long nz, int y, int x0, uint4 (&buf)[2]) {
-    buf[0] = buf[1] = make_uint4(0, 0, 0, 0);
-    if (t < 128) {
-      const int q = t & 3, x = x0 + 2 * (t >> 2);
-      const uint16_t* src = dout + ((nz * H + y) * (long long)W + x) * cout + co0 + 8 * q;
-      if (x < W) buf[0] = *reinterpret_cast<const uint4*>(src);
-      if (x + 1 < W) buf[1] = *reinterpret_cast<const uint4*>(src + cout);
+  auto store_dout = [&](int z) {
+    uint16_t* dst = lds + ((z + 3) % 3) * kWgPlane;
+#pragma unroll
+    for (int k = 0; k < DPF; ++k)
+      if (t + kWgThreads * k < DCH) *reinterpret_cast<uint4*>(dst + 8 * (t + kWgThreads * k)) = pd[k];
+  };
+  auto load_in = [&](long long nb, int z, int y0, int x0) {
+    const uint16_t* base = in + (nb * D + z) * H * (long long)W * cin + ci0;
+#pragma unroll
+    for (int k = 0; k < IPF; ++k) {
+      int it = t + kWgThreads * k;
+      asm volatile("" : "+v"(it));
+      const int q = PACK8 ? 0 : it & 3, v = (PACK8 ? it : it >> 2) % IRV, r = (PACK8 ? it : it >> 2) / IRV;
+      const int y = y0 + r, x = x0 + v - 1;
+      pi[k] = make_uint4(0, 0, 0, 0);
+      if (it < ICH && y < H && x >= 0 && x < W && ci0 + 8 * q < cin)
+        pi[k] = *reinterpret_cast<const uint4*>(base + ((long long)y * W + x) * cin + 8 * q);
     }
   };
-  auto store_dout = [&](const uint4 (&buf)[2]) {
-    if (t < 128) pair_store(sA, kRsA, t & 3, 2 * (t >> 2), buf[0], buf[1]);
-  };
-  auto load_row = [&](long long nz, int z, int yy, int x0, uint4 (&buf)[PB][2]) {
-    const int zz = z + dz;
-    const bool row_ok = zz >= 0 && zz < D && yy >= 0 && yy < H;
-    const long long base = ((nz + dz) * H + yy) * (long long)W;
+  auto store_in = [&]() {
 #pragma unroll
-    for (int k = 0; k < PB; ++k) {
-      const int it = lane + 64 * k;
-      const int q = it & 3, x = x0 - 8 + 2 * (it >> 2);
-      buf[k][0] = buf[k][1] = make_uint4(0, 0, 0, 0);
-      if (it < 2 * kRowB && row_ok && ci0 + 8 * q < cin) {
-        const uint16_t* src = in + (base + x) * cin + ci0 + 8 * q;
-        if (x >= 0 && x < W) buf[k][0] = *reinterpret_cast<const uint4*>(src);
-        if (x + 1 >= 0 && x + 1 < W) buf[k][1] = *reinterpret_cast<const uint4*>(src + cin);
+    for (int k = 0; k < IPF; ++k)
+      if (t + kWgThreads * k < ICH) *reinterpret_cast<uint4*>(lds + IN0 + 8 * (t + kWgThreads * k)) = pi[k];
+  };
+
+  // The whole walk for one role.  LAST: the fourth wave of a group.  The two instances run side by
+  // side and meet at the same barriers, two per step and two per round of the reduction; each has
+  // its own accumulators (one code path for both kept them twice, and spilled).
+  auto walk = [&](auto last) {
+  constexpr bool LAST = decltype(last)::value;
+  floatx16 acc[NACC], accb = floatx16{};
+#pragma unroll
+  for (int k = 0; k < NACC; ++k) acc[k] = floatx16{};
+  for (long long p = p0; p < p1; ++p) {
+    const int z = (int)(p % D);
+    const long long col = p / D;
+    const int xb = (int)(col % P.nxb), yb = (int)((col / P.nxb) % P.nyb);
+    const long long nb = col / ((long long)P.nxb * P.nyb);
+    const int x0 = xb * kWgX, y0 = yb * kWgY;
+    __syncthreads();  // the previous step's reads are done
+    if (p > p0 && z > 0) {
+      store_dout(z + 1);
+      store_in();
+    } else {  // a new column: all three planes
+#pragma unroll 1
+      for (int dz = -1; dz <= 1; ++dz) {
+        load_dout(nb, z + dz, y0, x0);
+        store_dout(z + dz);
       }
-    }
-  };
-  auto store_row = [&](int yy, const uint4 (&buf)[PB][2]) {
-    uint16_t* dst = sB[wave][(yy + 3) % 3];
-#pragma unroll
-    for (int k = 0; k < PB; ++k) {
-      const int it = lane + 64 * k;
-      if (it < 2 * kRowB) pair_store(dst, kRsB, it & 3, 2 * (it >> 2), buf[k][0], buf[k][1]);
-    }
-  };
-
-  // a segment continues the previous one's column when it is the next y of the same
-  // (n, z, segment); its dout row and its one new source row are then loaded during the
-  // previous segment's MFMAs
-  uint4 pfa[2], pfb[PB][2];
-  bool have = false;
-  long long prev_col = -1;
-  int prev_y = -2;
-  for (long long r = r0; r < r1; ++r) {
-    const int y = (int)(r % H);
-    const long long col = r / H;  // (n D + z) nseg + seg
-    const int seg = (int)(col % nseg);
-    const long long nz = col / nseg;  // n D + z
-    const int z = (int)(nz % D);
-    const int x0 = seg * kSeg;
-    const bool cont = col == prev_col && y == prev_y + 1;
-    prev_col = col;
-    prev_y = y;
-    __syncthreads();  // the previous segment's reads of LDS are done
-
-    if (have) {
-      store_dout(pfa);
-      store_row(y + 1, pfb);
-    } else {
-      uint4 tb[2];
-      load_dout(nz, y, x0, tb);
-      store_dout(tb);
-      for (int yy = cont ? y + 1 : y - 1; yy <= y + 1; ++yy) {
-        uint4 rb[PB][2];
-        load_row(nz, z, yy, x0, rb);
-        store_row(yy, rb);
-      }
-    }
-    have = r + 1 < r1 && y + 1 < H;  // the next segment continues this column
-    if (have) {
-      load_dout(nz, y + 1, x0, pfa);
-      load_row(nz, z, y + 2, x0, pfb);
+      load_in(nb, z, y0, x0);
+      store_in();
     }
     __syncthreads();
+    if (p + 1 < p1 && z + 1 < D) {  // the next step continues the column
+      load_dout(nb, z + 2, y0, x0);
+      load_in(nb, z + 1, y0, x0);
+    }
 
-    const int h = lane >> 5, c = lane & 31;
-    const uint16_t* pa = sA + trow(c, kRsA) + 32 * h;
-    if (do_bias && wave == 0) {
+    // the planes z + 1, z, z - 1 (dz = -1, 0, +1); staged row r is row y0 - 1 + r
+    const uint16_t* d1 = lds + ((z + 4) % 3) * kWgPlane + offA;
+    const uint16_t* d0 = lds + ((z + 3) % 3) * kWgPlane + offA;
+    const uint16_t* dm = lds + ((z + 2) % 3) * kWgPlane + offA;
+    auto rowA = [&](const uint16_t* plane, int r, int s) { return read_tr(plane + (r * kWgX + 16 * s) * 32, 32); };
+    auto rowB = [&](int r, int v) { return read_tr(lds + IN0 + offB + (r * IRV + v) * IC, IC); };
+    if constexpr (PACK8) {
+      const int s = wave & 1, ya = 4 * (wave >> 1);
+      uint4 a1[3], a0[3], am[3];  // rows y + 1, y, y - 1
+      a1[1] = rowA(d1, ya + 1, s), a1[2] = rowA(d1, ya, s);
+      a0[1] = rowA(d0, ya + 1, s), a0[2] = rowA(d0, ya, s);
+      am[1] = rowA(dm, ya + 1, s), am[2] = rowA(dm, ya, s);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float f[8];
-        unpack8(*reinterpret_cast<const uint4*>(pa + 8 * j), f);
+      for (int yy = 0; yy < 4; ++yy) {
+        const uint4 b = rowB(ya + yy, 16 * s);
+        a1[0] = rowA(d1, ya + yy + 2, s);
+        a0[0] = rowA(d0, ya + yy + 2, s);
+        am[0] = rowA(dm, ya + yy + 2, s);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) bsum += f[i];
+        for (int k = 0; k < 3; ++k) {
+          acc[k] = mfma16(a1[k], b, acc[k]);
+          acc[3 + k] = mfma16(a0[k], b, acc[3 + k]);
+          acc[6 + k] = mfma16(am[k], b, acc[6 + k]);
+        }
+        if (do_bias) accb = mfma16(a0[1], ones, accb);
+        a1[2] = a1[1], a1[1] = a1[0], a0[2] = a0[1], a0[1] = a0[0], am[2] = am[1], am[1] = am[0];
       }
-    }
-    const uint16_t* pb[3];
-    uint4 prv[3], cur[3];
+    } else {
+      const int role = wave & 3, ya = 8 * (wave >> 2);
+      if constexpr (!LAST) {  // dx = role - 1
+#pragma unroll 1
+        for (int s = 0; s < 2; ++s) {
+          uint4 a1[3], a0[3];
+          a1[1] = rowA(d1, ya + 1, s), a1[2] = rowA(d1, ya, s);
+          a0[1] = rowA(d0, ya + 1, s), a0[2] = rowA(d0, ya, s);
 #pragma unroll
-    for (int dy = 0; dy < 3; ++dy) {
-      pb[dy] = sB[wave][(y + dy + 2) % 3] + trow(c, kRsB) + 32 * h;  // element 8 + 32 h is voxel x0 + 32 h
-      prv[dy] = *reinterpret_cast<const uint4*>(pb[dy]);
-      cur[dy] = *reinterpret_cast<const uint4*>(pb[dy] + 8);
-    }
+          for (int yy = 0; yy < 8; ++yy) {
+            const uint4 b = rowB(ya + yy, 16 * s + role);
+            a1[0] = rowA(d1, ya + yy + 2, s);
+            a0[0] = rowA(d0, ya + yy + 2, s);
+            const uint4 am = rowA(dm, ya + yy + 2, s);
 #pragma unroll
-    for (int st = 0; st < kSeg / 16; ++st) {
-      const uint4 a = *reinterpret_cast<const uint4*>(pa + 8 * st);
+            for (int k = 0; k < 3; ++k) {
+              acc[k] = mfma16(a1[k], b, acc[k]);
+              acc[3 + k] = mfma16(a0[k], b, acc[3 + k]);
+            }
+            acc[6] = mfma16(am, b, acc[6]);
+            a1[2] = a1[1], a1[1] = a1[0], a0[2] = a0[1], a0[1] = a0[0];
+            __builtin_amdgcn_sched_barrier(0);  // not every row's reads at once
+          }
+        }
+      } else {  // (dz, dy) = (1, 0) and (1, 1) for every dx, and the bias
+#pragma unroll 1
+        for (int s = 0; s < 2; ++s) {
+          uint4 am1, am2 = rowA(dm, ya, s);
 #pragma unroll
-      for (int dy = 0; dy < 3; ++dy) {
-        const uint4 nxt = *reinterpret_cast<const uint4*>(pb[dy] + 16 + 8 * st);
-        acc[3 * dy + 0] = mfma16(a, shift_in_prev(prv[dy], cur[dy]), acc[3 * dy + 0]);  // voxels x - 1 ..
-        acc[3 * dy + 1] = mfma16(a, cur[dy], acc[3 * dy + 1]);
-        acc[3 * dy + 2] = mfma16(a, shift_in_next(cur[dy], nxt), acc[3 * dy + 2]);      // voxels x + 1 ..
-        prv[dy] = cur[dy];
-        cur[dy] = nxt;
+          for (int yy = 0; yy < 8; ++yy) {
+            am1 = rowA(dm, ya + yy + 1, s);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+              const uint4 b = rowB(ya + yy, 16 * s + k);
+              acc[k] = mfma16(am1, b, acc[k]);
+              acc[3 + k] = mfma16(am2, b, acc[3 + k]);
+            }
+            if (do_bias) acc[6] = mfma16(rowA(d0, ya + yy + 1, s), ones, acc[6]);
+            am2 = am1;
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
       }
     }
   }
 
-  // acc[3 dy + dx] row m = 8 (r / 4) + 4 h + r % 4 (co0 + m), column ci0 + lane % 32
-  {
-    const int h = lane >> 5, ci = ci0 + (lane & 31);
-    if (ci < cin) {
-      float* dst = part + ((long long)chunk * 27 + 9 * wave) * cout * cin;
+  // the waves' sums together, in a fixed order: PACK8 8 -> 4 -> 2 -> 1, else 8 -> 4 (the groups)
+  float* red = reinterpret_cast<float*>(lds);
+#pragma unroll 1
+  for (int half = 4; half >= (PACK8 ? 1 : 4); half /= 2) {
+    __syncthreads();
+    if (wave >= half && wave < 2 * half) {
+      float* slot = red + (wave - half) * NACC * 1024 + lane;
+#pragma unroll
+      for (int k = 0; k < NACC; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) slot[(k * 16 + r) * 64] = acc[k][r];
+    }
+    __syncthreads();
+    if (wave < half) {
+      const float* slot = red + wave * NACC * 1024 + lane;
+#pragma unroll
+      for (int k = 0; k < NACC; ++k)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[k][r] += slot[(k * 16 + r) * 64];
+    }
+  }
+  if (PACK8 && do_bias) {  // (every column of accb holds the sum)
+    __syncthreads();
+    if (c == 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) red[wave * 32 + (r / 4) * 8 + 4 * h + (r & 3)] = accb[r];
+    __syncthreads();
+    if (t < 32) {
+      float sum = red[t];
+      for (int w = 1; w < 8; ++w) sum += red[w * 32 + t];
+      bpart[(long long)chunk * cout + co0 + t] = sum;
+    }
+  }
+
+  // accumulator row m = 8 (r / 4) + 4 h + r % 4 (channel co0 + m), column c
+  float* dst = part + (long long)chunk * 27 * cout * cin;
+  if constexpr (PACK8) {
+    if (wave == 0 && c < 24) {
 #pragma unroll
       for (int k = 0; k < 9; ++k)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int co = co0 + (r / 4) * 8 + 4 * h + (r & 3);
-          dst[((long long)k * cout + co) * cin + ci] = acc[k][r];
-        }
+        for (int r = 0; r < 16; ++r)
+          dst[((long long)(3 * k + (c >> 3)) * cout + co0 + (r / 4) * 8 + 4 * h + (r & 3)) * cin + (c & 7)] = acc[k][r];
+    }
+  } else if (wave < 4) {
+    const int ci = ci0 + c;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+      const int tap = LAST ? 21 + k : 3 * k + wave;
+      if (LAST && k == 6) {
+        if (do_bias && c == 0)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) bpart[(long long)chunk * cout + co0 + (r / 4) * 8 + 4 * h + (r & 3)] = acc[k][r];
+      } else if (ci < cin) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          dst[((long long)tap * cout + co0 + (r / 4) * 8 + 4 * h + (r & 3)) * cin + ci] = acc[k][r];
+      }
     }
   }
-  if (do_bias) {
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(&sB[0][0][0]);
-    if (t < 64) red[t] = bsum;
-    __syncthreads();
-    if (t < 32) bpart[(long long)chunk * cout + co0 + t] = red[t] + red[t + 32];
+  };
+  if constexpr (PACK8) {
+    walk(std::false_type{});
+  } else {
+    if ((wave & 3) == 3)
+      walk(std::true_type{});
+    else
+      walk(std::false_type{});
   }
 }
 
@@ -1393,8 +1479,13 @@ extern "C" int surr_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float
   const WgradPlan p = wgrad_plan(n, d, h, wd, cin, cout);
   float* part = static_cast<float*>(scratch);
   float* bpart = part + (size_t)p.nchunks * 27 * cout * cin;
-  hipLaunchKernelGGL(wgrad_kernel, dim3(p.nchunks, p.tiles), dim3(192), 0, S(stream), in, dout, part,
-                     dbias ? bpart : nullptr, d, h, wd, cin, cout, p.nsr, p.nchunks, p.ci_tiles);
+  const dim3 grid(p.nchunks, p.tiles), block(kWgThreads);
+  if (cin == 8)
+    hipLaunchKernelGGL(wgrad_kernel<true>, grid, block, 0, S(stream), in, dout, part, dbias ? bpart : nullptr, d, h, wd,
+                       cin, cout, p);
+  else
+    hipLaunchKernelGGL(wgrad_kernel<false>, grid, block, 0, S(stream), in, dout, part, dbias ? bpart : nullptr, d, h, wd,
+                       cin, cout, p);
   launch_chunk_sums(part, dw, 27LL * cout * cin, bpart, dbias, (long long)cout, p.nchunks, S(stream));
   return done();
 }
