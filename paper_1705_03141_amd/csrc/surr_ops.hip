@@ -839,7 +839,9 @@ __global__ void flip_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict
 //
 // One block per compute unit: 256 partial sums in all, a third of the time of a full-resolution
 // layer at 512.  The next step's planes are loaded during the present one's MFMAs.  Measured
-// (with the sum of the partials), 32 -> 32 channels on 1x256x64x64: WGRADFIG
+// (with the sum of the partials), 32 -> 32 channels on 1x256x64x64 79 us, 730 TFLOP/s, against 114 us
+// for the kernel before (transposes while staging, three waves, 512 partial sums); 8 -> 32 50
+// against 121, 32 -> 64 on 1x128x32x32 33 against 64, 64 -> 64 on 1x64x16x16 29 against 45.
 constexpr int kWgX = 32, kWgY = 16;               // voxels and rows of a tile
 constexpr int kWgThreads = 512, kWgBlocks = 256;  // one resident block on each of 256 compute units
 constexpr int kWgRow = kWgX * 32, kWgPlane = (kWgY + 2) * kWgRow;  // elements of a staged dout row, plane
@@ -1281,15 +1283,19 @@ __global__ void up_bwd_kernel(const uint16_t* __restrict__ dout, const uint16_t*
   *reinterpret_cast<uint4*>(din + vc * c + ch) = pack8(s);
 }
 
+// A block covers 256 voxels: each thread forms the errors of one, and the block then writes the
+// gradient's 16-byte words in memory order (used <= 8; a thread that wrote its voxel's row by
+// itself scattered them 2 stride bytes apart: 69 us for 2^20 voxels of 32 channels, 61 us now, of which 134 MB of pred lines are the most).
 __global__ void __launch_bounds__(256) mse_kernel(const float* __restrict__ pred, const float* __restrict__ target,
                                                   uint16_t* __restrict__ dpred, float* __restrict__ loss_part,
                                                   long long count, int stride, int used) {
   __shared__ float s[256];
+  __shared__ uint4 first[256];  // the first 8 channels of each voxel's gradient
   const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
   float e2 = 0.0f;
   if (v < count) {
     const float scale = 2.0f / ((float)count * (float)used);
-    for (int k0 = 0; k0 < stride; k0 += 8) {
+    for (int k0 = 0; k0 < (used > 8 ? stride : 8); k0 += 8) {
       float g[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -1300,11 +1306,22 @@ __global__ void __launch_bounds__(256) mse_kernel(const float* __restrict__ pred
           g[j] = scale * e;
         }
       }
-      *reinterpret_cast<uint4*>(dpred + v * stride + k0) = pack8(g);
+      if (used > 8)
+        *reinterpret_cast<uint4*>(dpred + v * stride + k0) = pack8(g);
+      else
+        first[threadIdx.x] = pack8(g);
     }
   }
   s[threadIdx.x] = e2;
   __syncthreads();
+  if (used <= 8) {
+    const int words = stride / 8;
+    const long long left = count - (long long)blockIdx.x * 256;
+    const int n = (int)(left < 256 ? left : 256) * words;
+    uint4* dst = reinterpret_cast<uint4*>(dpred) + (long long)blockIdx.x * 256 * words;
+    for (int i = threadIdx.x; i < n; i += 256)
+      dst[i] = i % words == 0 ? first[i / words] : make_uint4(0, 0, 0, 0);
+  }
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) s[threadIdx.x] += s[threadIdx.x + o];
     __syncthreads();
