@@ -3,12 +3,12 @@
 // the small element-wise operators of the encoder-decoder and its training.
 //
 // Convolution.  out[v][co] = sum_tap sum_ci in[v + off(tap)][ci] w[tap][co][ci] is a GEMM with
-// M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_ring_kernel and
-// conv_staged_kernel for activations, conv_slide_kernel for data gradients and FP32 results,
-// wgrad_kernel) stage their operands through LDS and issue v_mfma_f32_32x32x16_bf16;
+// M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_slide_kernel;
+// conv_ring_kernel for the 8-channel input; wgrad_kernel) stage their operands through LDS and
+// issue v_mfma_f32_32x32x16_bf16; conv_staged_kernel takes small volumes of 64 channels, and
 // conv_fwd_kernel, the direct form with one wave per 32 voxels x 32 output channels and
-// v_mfma_f32_32x32x8_bf16 fed from global memory, serves channel counts the others do not take
-// (cin = 128, and planes too large for 32-bit offsets).
+// v_mfma_f32_32x32x8_bf16 fed from global memory, channel counts the others do not take (cin = 128,
+// and planes too large for 32-bit offsets).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -533,40 +533,51 @@ void launch_staged(const uint16_t* in, const uint16_t* w, const float* bias, uin
                      cout, relu, ntiles);
 }
 
-// ---------------------------------------------------------------- forward convolution, sliding
-// For cin in {8, 16, 32, 64}.  A block owns a co tile of 32, a tile of ROWS x SEG output columns
-// and a range of z, and sweeps the input planes of that range.  Each staged plane is used once,
-// for all the outputs it contributes to: a wave of R rows x 32 voxels keeps the accumulators of
-// three output planes (z - 1, z, z + 1) in registers, and a fragment of voxels read from LDS
-// feeds up to 9 MFMAs (3 dz x 3 dy), one of weights R.  No partial sums are exchanged between
-// waves.  What bounds it is the LDS reads beside the matrix cores: (9 + R + 2) KB per 9 R
-// v_mfma_f32_32x32x16_bf16 of 32 cycles each, 0.72 of the LDS rate at R = 2.
+// ---------------------------------------------------------------- convolution, sliding
+// For cin in {32, 64}: activations, FP32 results and data gradients.  A block of eight waves owns a
+// co tile of 32, a tile of ROWS x SEG output columns and a range of z, and sweeps the input planes of
+// that range.  Each staged plane is used once, for all the outputs it contributes to: a wave (one
+// row of 32 voxels) keeps the accumulators of three output planes (z - 1, z, z + 1) in registers,
+// and a fragment of voxels read from LDS feeds three MFMAs.  No partial sums pass between waves.
 //
-// The weights of the co tile stay in LDS in fragment order (1 KB per tap and 16 channels,
-// read without conflicts); the plane of voxels has a voxel stride of CP + 8 elements (4 x an odd
-// number of dwords, so that groups of 8 lanes reading 16 bytes cover all banks once).  The
-// weights are the first operand, so a lane holds 4 x 4 consecutive output channels of one voxel
-// and stores 8 bytes (16 in FP32) at a time.  The next plane's global loads are issued before the
-// MFMAs of the present one.  With 8 input channels the upper half of a 16-channel fragment is
-// zero on both sides.
+// The sums are in the order of the kernels that split the taps over the waves of a block (the ring
+// and staged kernels), so that results stay bitwise what they were: another order moves one BF16
+// activation in 10^4 by an ulp, which the network carries to 5e-4 of its prediction.  The K-steps
+// k = tap * SL + slice fall into NCHAIN chains of consecutive k, each summed from zero; with 64
+// channels the 8 chains are added in order, with 32 the 4 chains c as ((c_w + c_w-1) + c_w-2) +
+// c_w-3, indices modulo 4, w = 2 (y % 2) + x / 32 % 2; the bias comes last.  So the taps of a plane
+// are walked in order, and unfinished chains travel with their output: two accumulators per output
+// with 64 channels (sum and chain), up to four with 32, nine for the three planes, which leaves
+// room for one row per wave.
 //
-// Measured, data gradient behind a ReLU mask against the kernel it replaces and its separate mask
-// pass: 32 -> 32 channels on 1x256x64x64 125 -> 93 us (of which the mask's bytes are 14), 64 -> 32
-// on 1x128x32x32 69 -> 28 us, 32 -> 64 59 -> 26 us, 64 -> 64 on 1x64x16x16 33 -> 18 us; FP32 result
-// 32 -> 32 on 1x256x64x64 98 -> 69 us.  Without its stores it takes 50 us, 1160 TFLOP/s.
+// The weights of the co tile stay in LDS in fragment order (1 KB per tap and 16 channels, read
+// without conflicts); the plane of voxels has a voxel stride of CIN + 8 elements (4 x an odd number
+// of dwords, so that groups of 8 lanes reading 16 bytes cover all banks once).  The weights are the
+// first operand, so a lane holds 4 x 4 consecutive output channels of one voxel and stores 8 bytes
+// (16 in FP32) at a time; a data gradient's ReLU mask is applied there.  The next plane's global
+// loads are issued before the MFMAs of the present one.
 //
-// CIN: input channels; XT x WY waves, each 32 voxels x R rows; NBUF staged planes (two where they
+// What bounds it is the rate the card sustains on the matrix cores: an 8192^3 BF16 product reaches
+// 1180 TFLOP/s, a form of this kernel without its stores 1160.  Measured against the ring and
+// staged kernels (and their separate mask pass): 32 -> 32 on 1x256x64x64 105 -> 64 us (901 TFLOP/s),
+// FP32 result 98 -> 75, masked data gradient 125 -> 93; 1x128x32x32: 32 -> 64 51 -> 22 us, 64 -> 32
+// 64 -> 24; 64 -> 64 on 1x64x16x16 31 -> 17 us.  Two rows per wave with one accumulator per output (the
+// taps in any order) took 64 us for the first and 86 for the masked gradient; four rows in four
+// waves 85 us.
+//
+// CIN: input channels; XT x WY waves, each 32 voxels of a row; NBUF staged planes (two where they
 // fit beside the weights: one barrier per plane instead of two).
 template <int CIN_, int XT_, int WY_, int NBUF_>
 struct SlideConv {
-  static constexpr int CIN = CIN_, XT = XT_, WY = WY_, NBUF = NBUF_, R = 2;
+  static constexpr int CIN = CIN_, XT = XT_, WY = WY_, NBUF = NBUF_;
+  static constexpr int NCHAIN = CIN == 64 ? 8 : 4;
+  static constexpr int NA = CIN == 64 ? 2 : 4;  // accumulators per output
   static constexpr int NW = XT * WY, NT = 64 * NW;
-  static constexpr int CP = CIN < 16 ? 16 : CIN;  // channels of a staged voxel
-  static constexpr int SEG = 32 * XT, ROWS = WY * R;
+  static constexpr int SEG = 32 * XT, ROWS = WY;
   static constexpr int RV = SEG + 2, SR = ROWS + 2;  // staged voxels per row, rows
-  static constexpr int VS = CP + 8;                  // staged voxel stride (elements)
-  static constexpr int SL = CP / 16;                 // 16-channel slices
-  static constexpr int Q = CIN / 8;                  // 16-byte chunks of a voxel in memory
+  static constexpr int VS = CIN + 8;                 // staged voxel stride (elements)
+  static constexpr int SL = CIN / 16;                // 16-channel slices
+  static constexpr int Q = CIN / 8;                  // 16-byte chunks of a voxel
   static constexpr int PLANE = SR * RV * VS;         // elements of a staged plane
   static constexpr int CHUNKS = SR * RV * Q;
   static constexpr int PF = (CHUNKS + NT - 1) / NT;  // chunks per thread
@@ -580,7 +591,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
     const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
     const uint16_t* __restrict__ relu_y, uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W,
     int cout, int relu, int nzc, int zlen) {
-  constexpr int R = P::R, SL = P::SL, Q = P::Q;
+  constexpr int SL = P::SL, Q = P::Q;
   __shared__ __align__(16) uint16_t sw[P::WELEMS];
   __shared__ __align__(16) uint16_t sv[P::NBUF * P::PLANE];
   __shared__ __align__(16) float sb[32];
@@ -601,28 +612,6 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
   const int x0 = seg * P::SEG, y0 = yb * P::ROWS, za = zc * zlen, zb = min(D, za + zlen);
   const long long plane_elems = (long long)H * W * P::CIN;
   const uint16_t* in_n = in + nb * D * plane_elems;
-
-  // weights and bias of the co tile
-  if constexpr (P::CIN < P::CP) {
-    for (int i = t; i < P::WELEMS / 8; i += P::NT) *reinterpret_cast<uint4*>(sw + 8 * i) = make_uint4(0, 0, 0, 0);
-    for (int i = t; i < P::NBUF * P::PLANE / 8; i += P::NT) *reinterpret_cast<uint4*>(sv + 8 * i) = make_uint4(0, 0, 0, 0);
-    __syncthreads();
-  }
-  {
-    constexpr int WCH = 27 * 32 * Q, WPT = (WCH + P::NT - 1) / P::NT;
-    uint4 wr[WPT];
-#pragma unroll
-    for (int k = 0; k < WPT; ++k) {
-      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
-      wr[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
-    }
-#pragma unroll
-    for (int k = 0; k < WPT; ++k) {
-      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
-      *reinterpret_cast<uint4*>(sw + (tap * SL + q / 2) * 512 + ((q & 1) * 32 + co) * 8) = wr[k];
-    }
-  }
-  if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
 
   // the staged chunks this thread moves: offset within an input plane, -1 outside of it
   int src[P::PF], dst[P::PF];
@@ -650,59 +639,72 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
         *reinterpret_cast<uint4*>(d + dst[k]) = pf[k];
   };
 
-  floatx16 acc[3][R];  // outputs p + 1, p, p - 1 of the staged plane p
+  if (za > 0) load(za - 1);
+  // weights and bias of the co tile (after the loads of the first plane: all are in flight together)
+  {
+    constexpr int WCH = 27 * 32 * Q, WPT = (WCH + P::NT - 1) / P::NT;
+    uint4 wr[WPT];
 #pragma unroll
-  for (int r = 0; r < R; ++r) acc[0][r] = acc[1][r] = acc[2][r] = floatx16{};
+    for (int k = 0; k < WPT; ++k) {
+      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
+      wr[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
+    }
+#pragma unroll
+    for (int k = 0; k < WPT; ++k) {
+      const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
+      *reinterpret_cast<uint4*>(sw + (tap * SL + q / 2) * 512 + ((q & 1) * 32 + co) * 8) = wr[k];
+    }
+  }
+  if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
+
+  constexpr int NA = P::NA;
+  floatx16 acc[3][NA];  // outputs p + 1, p, p - 1 of the staged plane p
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+#pragma unroll
+    for (int a = 0; a < NA; ++a) acc[d][a] = floatx16{};
 
   // every MFMA of plane p towards the output planes in MASK (bit dz: output p + 1 - dz)
   auto plane_mfmas = [&](auto M, int p) {
     constexpr int MASK = decltype(M)::value;
-    int b0 = (P::NBUF == 2 ? (p & 1) * P::PLANE : 0) + (wy * R * P::RV + xt * 32 + c) * P::VS + 8 * h, w0 = lane * 8;
+    int b0 = (P::NBUF == 2 ? (p & 1) * P::PLANE : 0) + (wy * P::RV + xt * 32 + c) * P::VS + 8 * h, w0 = lane * 8;
     asm volatile("" : "+v"(b0), "+v"(w0));
+    auto chain = [](int k) {  // of K-step k
+      int ch = 0;
+      for (int w = 1; w < P::NCHAIN; ++w) ch += k >= 27 * SL * w / P::NCHAIN;
+      return ch;
+    };
 #pragma unroll
-    for (int sl = 0; sl < SL; ++sl)
+    for (int tp = 0; tp < 9; ++tp)
 #pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        uint4 wf[3][3], vf[R + 2];
-#pragma unroll
-        for (int r = 0; r < R + 2; ++r)
-          vf[r] = *reinterpret_cast<const uint4*>(sv + b0 + (r * P::RV + dx) * P::VS + sl * 16);
+      for (int sl = 0; sl < SL; ++sl) {
+        const uint4 vf =
+            *reinterpret_cast<const uint4*>(sv + b0 + ((tp / 3) * P::RV + tp % 3) * P::VS + sl * 16);
+        uint4 wf[3];
 #pragma unroll
         for (int dz = 0; dz < 3; ++dz)
+          if ((MASK >> dz) & 1) wf[dz] = *reinterpret_cast<const uint4*>(sw + w0 + ((dz * 9 + tp) * SL + sl) * 512);
 #pragma unroll
-          for (int dy = 0; dy < 3; ++dy)
-            if ((MASK >> dz) & 1)
-              wf[dz][dy] = *reinterpret_cast<const uint4*>(sw + w0 + (((dz * 3 + dy) * 3 + dx) * SL + sl) * 512);
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy)
-#pragma unroll
-          for (int dz = 0; dz < 3; ++dz)
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-              if ((MASK >> dz) & 1) acc[dz][r] = mfma16(wf[dz][dy], vf[r + dy], acc[dz][r]);
+        for (int dz = 0; dz < 3; ++dz)
+          if ((MASK >> dz) & 1) {
+            const int k = (dz * 9 + tp) * SL + sl, ch = chain(k), a = NA == 2 ? 1 : ch;
+            const bool begins = k == 0 || chain(k - 1) != ch;
+            if (NA == 2 && begins && k > 0) acc[dz][0] += acc[dz][1];
+            acc[dz][a] = mfma16(wf[dz], vf, begins ? floatx16{} : acc[dz][a]);
+          }
+        if (tp % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // bounds the reads in flight
       }
   };
 
-  __syncthreads();
-  if (za > 0) load(za - 1);
   if (za > 0) store(za - 1);
   __syncthreads();
 #pragma unroll 1
   for (int p = za - 1; p <= zb; ++p) {
     const bool more = p + 1 <= zb && p + 1 < D;
     if (more) load(p + 1);
-    // a new output plane starts from the bias: lane (h, c) holds channels 8 g + 4 h .. + 3
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        acc[0][r][4 * g + 0] = b4.x;
-        acc[0][r][4 * g + 1] = b4.y;
-        acc[0][r][4 * g + 2] = b4.z;
-        acc[0][r][4 * g + 3] = b4.w;
-      }
-    }
+    // the chains that no earlier plane has begun
+    acc[0][0] = acc[0][1] = floatx16{};
+    if constexpr (NA == 4) acc[1][2] = acc[2][3] = floatx16{};
     if (p >= 0 && p < D) {
       const int mask = (p + 1 < zb ? 1 : 0) | (p >= za && p < zb ? 2 : 0) | (p > za ? 4 : 0);
       switch (mask) {
@@ -714,52 +716,51 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
         case 6: plane_mfmas(std::integral_constant<int, 6>{}, p); break;
       }
     }
-    const int x = x0 + xt * 32 + c, ya = y0 + wy * R;
-    // voxel (p - 1, ya, x), channel co0 + 4 h: output plane p - 1 is complete
-    const long long o0 = (((nb * D + p - 1) * H + ya) * (long long)W + x) * cout + co0 + 4 * h;
-    const long long orow = (long long)W * cout;
-    uint2 m[R][4];
-    if (MASKED && p > za) {  // in flight while the next plane goes to LDS
+    const int x = x0 + xt * 32 + c, y = y0 + wy;
+    const bool put = p > za && y < H && x < W;  // output plane p - 1 is complete
+    const long long o = (((nb * D + p - 1) * H + y) * (long long)W + x) * cout + co0 + 4 * h;
+    uint2 m[4];
+    if (MASKED && put) {  // in flight while the next plane goes to LDS
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          m[r][g] = make_uint2(0, 0);
-          if (ya + r < H && x < W) m[r][g] = *reinterpret_cast<const uint2*>(relu_y + o0 + r * orow + 8 * g);
-        }
+      for (int g = 0; g < 4; ++g) m[g] = *reinterpret_cast<const uint2*>(relu_y + o + 8 * g);
     }
     if constexpr (P::NBUF == 1) __syncthreads();  // every wave is done with the plane
     if (more) store(p + 1);
-    if (p > za) {
+    if (put) {
+      floatx16 v;
+      if constexpr (NA == 2) {
+        v = acc[2][0] + acc[2][1];
+      } else {
+        const floatx16 c0 = acc[2][0], c1 = acc[2][1], c2 = acc[2][2], c3 = acc[2][3];
+        const int half = ((x0 >> 5) + xt) & 1;
+        if ((wy & 1) == 0)  // (y0 is even)
+          v = half ? ((c1 + c0) + c3) + c2 : ((c0 + c3) + c2) + c1;
+        else
+          v = half ? ((c3 + c2) + c1) + c0 : ((c2 + c1) + c0) + c3;
+      }
 #pragma unroll
-      for (int r = 0; r < R; ++r)
-        if (ya + r < H && x < W) {
-          const long long o = o0 + r * orow;
+      for (int g = 0; g < 4; ++g) {  // channels 8 g + 4 h .. + 3
+        const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
+        float f[4] = {v[4 * g + 0] + b4.x, v[4 * g + 1] + b4.y, v[4 * g + 2] + b4.z, v[4 * g + 3] + b4.w};
+        if (relu)
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            float f[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              f[k] = acc[2][r][4 * g + k];
-              if (relu) f[k] = fmaxf(f[k], 0.0f);
-            }
-            if (out_f32) {
-              *reinterpret_cast<float4*>(out_f32 + o + 8 * g) = make_float4(f[0], f[1], f[2], f[3]);
-            } else {
-              uint2 u = make_uint2(pack2(f[0], f[1]), pack2(f[2], f[3]));
-              if (MASKED) {  // the gradient of the pre-activation: 0 where the ReLU output is not positive
-                u.x &= positive_mask(m[r][g].x);
-                u.y &= positive_mask(m[r][g].y);
-              }
-              *reinterpret_cast<uint2*>(out + o + 8 * g) = u;
-            }
+          for (int k = 0; k < 4; ++k) f[k] = fmaxf(f[k], 0.0f);
+        if (out_f32) {
+          *reinterpret_cast<float4*>(out_f32 + o + 8 * g) = make_float4(f[0], f[1], f[2], f[3]);
+        } else {
+          uint2 u = make_uint2(pack2(f[0], f[1]), pack2(f[2], f[3]));
+          if (MASKED) {  // the gradient of the pre-activation: 0 where the ReLU output is not positive
+            u.x &= positive_mask(m[g].x);
+            u.y &= positive_mask(m[g].y);
           }
+          *reinterpret_cast<uint2*>(out + o + 8 * g) = u;
         }
+      }
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      acc[2][r] = acc[1][r];
-      acc[1][r] = acc[0][r];
+    for (int a = 0; a < NA; ++a) {
+      acc[2][a] = acc[1][a];
+      acc[1][a] = acc[0][a];
     }
     __syncthreads();
   }
@@ -794,16 +795,17 @@ void launch_slide(const uint16_t* in, const uint16_t* w, const float* bias, cons
                        cout, relu, nzc, zlen);
 }
 
-// Tiles of 8 rows x 64 voxels or 16 rows x 32, whichever covers the plane with less padding.
-template <int CIN>
-void launch_slide_tile(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
-                       float* out_f32, int n, int d, int h, int wd, int cout, int relu, hipStream_t s) {
-  const long long wide = (long long)((wd + 63) / 64 * 64) * ((h + 7) / 8 * 8);
-  const long long tall = (long long)((wd + 31) / 32 * 32) * ((h + 15) / 16 * 16);
+// 32 channels: tiles of 4 rows x 64 voxels or 8 rows x 32, whichever covers the plane with less
+// padding.
+inline void launch_slide32(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y,
+                           uint16_t* out, float* out_f32, int n, int d, int h, int wd, int cout, int relu,
+                           hipStream_t s) {
+  const long long wide = (long long)((wd + 63) / 64 * 64) * ((h + 3) / 4 * 4);
+  const long long tall = (long long)((wd + 31) / 32 * 32) * ((h + 7) / 8 * 8);
   if (wide <= tall)
-    launch_slide<SlideConv<CIN, 2, 4, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+    launch_slide<SlideConv<32, 2, 4, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
   else
-    launch_slide<SlideConv<CIN, 1, 8, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+    launch_slide<SlideConv<32, 1, 8, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
 }
 
 // w_t[tap'][ci][co] = w[26 - tap'][co][ci]
@@ -1408,32 +1410,18 @@ inline int done() { return hipGetLastError() == hipSuccess ? 0 : -2; }
 }  // namespace
 
 namespace {
-// grad: a data gradient; relu_y: the result is 0 where it is not positive (BF16 output)
+// relu_y: the result is 0 where it is not positive (BF16 output)
 int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
-                  float* out_f32, int n, int d, int h, int wd, int cin, int cout, int relu, bool grad, void* stream) {
+                  float* out_f32, int n, int d, int h, int wd, int cin, int cout, int relu, void* stream) {
   if (n < 1 || d < 1 || h < 1 || wd < 1 || cin < 8 || cin % 8 || cout < 32 || cout % 32 || !in || !w ||
       (!out && !out_f32))
     return -1;
   const long long nvox = (long long)n * d * h * wd;
   hipStream_t s = S(stream);
   const bool small_plane = (long long)h * wd * cin < (1LL << 31);  // 32-bit offsets within an input plane
-  // The sliding kernel takes gradients and FP32 results (up to 2.5 times as fast as the ring and
-  // staged kernels, measured below), and moves 16 bytes at a time.  BF16 activations keep those
-  // kernels: another order of the sums moves one in 10^4 of them by a BF16 ulp, which the
-  // network carries to 5e-4 of its prediction (measured), and predictions stay reproducible bit
-  // for bit.
-  const bool slide = (out_f32 || grad) && small_plane && aligned16(in) && aligned16(w) &&
+  // the sliding kernel moves 16 bytes at a time, and 8 of its BF16 output and mask
+  const bool slide = small_plane && aligned16(in) && aligned16(w) &&
                      (out_f32 ? aligned16(out_f32) : ((uintptr_t)out & 7) == 0) && ((uintptr_t)relu_y & 7) == 0;
-  if (slide && cin <= 64) {
-    switch (cin) {
-      case 8: launch_slide_tile<8>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
-      case 16: launch_slide_tile<16>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
-      case 32: launch_slide_tile<32>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s); return done();
-      case 64:
-        launch_slide<SlideConv<64, 1, 4, 1>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
-        return done();
-    }
-  }
   switch (cin) {
     case 8:
       if (small_plane)
@@ -1448,12 +1436,25 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
         launch_staged<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       break;
     case 32:
+      if (slide) {
+        launch_slide32(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+        return done();
+      }
       if (small_plane)
         launch_ring<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
         launch_staged<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       break;
-    case 64: launch_staged<64>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s); break;
+    case 64:
+      // few tiles: the staged kernel, whose blocks load no more than their own tile's share of the
+      // weights and all three planes at once (1x5x9x33, 50 tiles x 2: 11 against 15 us; 1x64x16x16,
+      // 512 x 2: 31 against 17)
+      if (slide && (long long)n * d * ((wd + 31) / 32) * ((h + 1) / 2) * (cout / 32) > 256) {
+        launch_slide<SlideConv<64, 1, 8, 1>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+        return done();
+      }
+      launch_staged<64>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
+      break;
     case 128: launch_conv<128>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s); break;
     default: return -1;
   }
@@ -1464,7 +1465,7 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
 
 extern "C" int surr_conv3d_fwd(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32,
                                int n, int d, int h, int wd, int cin, int cout, int relu, void* stream) {
-  return conv_dispatch(in, w, bias, nullptr, out, out_f32, n, d, h, wd, cin, cout, relu, false, stream);
+  return conv_dispatch(in, w, bias, nullptr, out, out_f32, n, d, h, wd, cin, cout, relu, stream);
 }
 
 extern "C" int surr_conv3d_flip_weights(const uint16_t* w, uint16_t* w_t, int cin, int cout, void* stream) {
@@ -1478,7 +1479,7 @@ extern "C" int surr_conv3d_dgrad(const uint16_t* dout, const uint16_t* w_t, cons
                                  int d, int h, int wd, int cin, int cout, void* stream) {
   // the forward convolution of dout (cout channels) with w_t gives din (cin channels)
   if (!din) return -1;
-  return conv_dispatch(dout, w_t, nullptr, relu_y, din, nullptr, n, d, h, wd, cout, cin, 0, true, stream);
+  return conv_dispatch(dout, w_t, nullptr, relu_y, din, nullptr, n, d, h, wd, cout, cin, 0, stream);
 }
 
 extern "C" size_t surr_conv3d_wgrad_scratch_bytes(int n, int d, int h, int wd, int cin, int cout) {
