@@ -843,7 +843,9 @@ __global__ void flip_kernel(const uint16_t* __restrict__ w, uint16_t* __restrict
 // layer at 512.  The next step's planes are loaded during the present one's MFMAs.  Measured
 // (with the sum of the partials), 32 -> 32 channels on 1x256x64x64 79 us, 730 TFLOP/s, against 114 us
 // for the kernel before (transposes while staging, three waves, 512 partial sums); 8 -> 32 50
-// against 121, 32 -> 64 on 1x128x32x32 33 against 64, 64 -> 64 on 1x64x16x16 29 against 45.
+// against 121, 32 -> 64 on 1x128x32x32 33 against 64, 64 -> 64 on 1x64x16x16 29 against 45.  Rows and
+// half-rows of a tile beyond the lattice are passed over, which is what small volumes spend their
+// time on otherwise: 32 -> 64 on 1x3x100 14.1 us with them, 10.2 without (12 before).
 constexpr int kWgX = 32, kWgY = 16;               // voxels and rows of a tile
 constexpr int kWgThreads = 512, kWgBlocks = 256;  // one resident block on each of 256 compute units
 constexpr int kWgRow = kWgX * 32, kWgPlane = (kWgY + 2) * kWgRow;  // elements of a staged dout row, plane
@@ -982,12 +984,14 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
     auto rowB = [&](int r, int v) { return read_tr(lds + IN0 + offB + (r * IRV + v) * IC, IC); };
     if constexpr (PACK8) {
       const int s = wave & 1, ya = 4 * (wave >> 1);
+      const int rows = 16 * s < W - x0 ? H - y0 - ya : 0;
       uint4 a1[3], a0[3], am[3];  // rows y + 1, y, y - 1
       a1[1] = rowA(d1, ya + 1, s), a1[2] = rowA(d1, ya, s);
       a0[1] = rowA(d0, ya + 1, s), a0[2] = rowA(d0, ya, s);
       am[1] = rowA(dm, ya + 1, s), am[2] = rowA(dm, ya, s);
 #pragma unroll
       for (int yy = 0; yy < 4; ++yy) {
+        if (yy >= rows) break;
         const uint4 b = rowB(ya + yy, 16 * s);
         a1[0] = rowA(d1, ya + yy + 2, s);
         a0[0] = rowA(d0, ya + yy + 2, s);
@@ -1003,14 +1007,16 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
       }
     } else {
       const int role = wave & 3, ya = 8 * (wave >> 2);
+      const int rows = H - y0 - ya, halves = W - x0 > 16 ? 2 : 1;  // the rest of the tile is 0
       if constexpr (!LAST) {  // dx = role - 1
 #pragma unroll 1
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < halves; ++s) {
           uint4 a1[3], a0[3];
           a1[1] = rowA(d1, ya + 1, s), a1[2] = rowA(d1, ya, s);
           a0[1] = rowA(d0, ya + 1, s), a0[2] = rowA(d0, ya, s);
 #pragma unroll
           for (int yy = 0; yy < 8; ++yy) {
+            if (yy >= rows) break;
             const uint4 b = rowB(ya + yy, 16 * s + role);
             a1[0] = rowA(d1, ya + yy + 2, s);
             a0[0] = rowA(d0, ya + yy + 2, s);
@@ -1027,10 +1033,11 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
         }
       } else {  // (dz, dy) = (1, 0) and (1, 1) for every dx, and the bias
 #pragma unroll 1
-        for (int s = 0; s < 2; ++s) {
+        for (int s = 0; s < halves; ++s) {
           uint4 am1, am2 = rowA(dm, ya, s);
 #pragma unroll
           for (int yy = 0; yy < 8; ++yy) {
+            if (yy >= rows) break;
             am1 = rowA(dm, ya + yy + 1, s);
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
@@ -1047,10 +1054,11 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
     }
   }
 
-  // the waves' sums together, in a fixed order: PACK8 8 -> 4 -> 2 -> 1, else 8 -> 4 (the groups)
+  // the waves' sums together, in a fixed order: PACK8 8 -> 4 -> 2 -> 1, else 8 -> 4 (the groups);
+  // waves whose rows all lie beyond the lattice hold zeros and are left out
   float* red = reinterpret_cast<float*>(lds);
 #pragma unroll 1
-  for (int half = 4; half >= (PACK8 ? 1 : 4); half /= 2) {
+  for (int half = H > 8 ? 4 : PACK8 ? (H > 4 ? 2 : 1) : 0; half >= (PACK8 ? 1 : 4); half /= 2) {
     __syncthreads();
     if (wave >= half && wave < 2 * half) {
       float* slot = red + (wave - half) * NACC * 1024 + lane;
@@ -1498,7 +1506,10 @@ extern "C" int surr_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float
   float* part = static_cast<float*>(scratch);
   float* bpart = part + (size_t)p.nchunks * 27 * cout * cin;
   const dim3 grid(p.nchunks, p.tiles), block(kWgThreads);
-  if (cin == 8)
+  // PACK8 has a third of the MFMAs but adds up eight waves' sums at the end, not two.  With one step
+  // per block that is no gain: 8 -> 32 channels on 3x5x5 voxels 12.1 us with it and 9.7 without, on
+  // 256x16x32 (256 steps) 21.1 and 21.0, on 256x16x64 24.8 and 28.0.
+  if (cin == 8 && p.steps > kWgBlocks)
     hipLaunchKernelGGL(wgrad_kernel<true>, grid, block, 0, S(stream), in, dout, part, dbias ? bpart : nullptr, d, h, wd,
                        cin, cout, p);
   else
