@@ -4,7 +4,7 @@
 //
 // Convolution.  out[v][co] = sum_tap sum_ci in[v + off(tap)][ci] w[tap][co][ci] is a GEMM with
 // M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_slide_kernel;
-// conv_ring_kernel for the 8-channel input; wgrad_kernel) stage their operands through LDS and
+// conv_box_kernel for the 8-channel input; wgrad_kernel) stage their operands through LDS and
 // issue v_mfma_f32_32x32x16_bf16; conv_staged_kernel takes small volumes of 64 channels, and
 // conv_fwd_kernel, the direct form with one wave per 32 voxels x 32 output channels and
 // v_mfma_f32_32x32x8_bf16 fed from global memory, channel counts the others do not take (cin = 128,
@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(64 * StagedConv<CIN>::NW, 2) conv_staged_kerne
 }
 
 // ---------------------------------------------------------------- forward convolution, z ring
-// For cin in {8, 16, 32}: as the staged kernel (four waves split the K-steps, weights in
+// For cin in {8, 16, 32}, where a buffer is not aligned to 16 bytes: as the staged kernel (four waves split the K-steps, weights in
 // registers, output tiles of two rows x 64 voxels), but a block owns a column (n, row pair,
 // segment) and sweeps a range of z: the three input planes z - 1, z, z + 1 (4 rows x 66
 // voxels each) live in a ring in LDS, so each output plane stages one new plane, and the
@@ -806,6 +806,168 @@ inline void launch_slide32(const uint16_t* in, const uint16_t* w, const float* b
     launch_slide<SlideConv<32, 2, 4, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
   else
     launch_slide<SlideConv<32, 1, 8, 2>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
+}
+
+// ---------------------------------------------------------------- convolution, few channels
+// For cin in {8, 16}.  A block of four waves stages a box of the input -- ZT + 2 planes, 6 rows and 66
+// voxels, every load in flight at once and one barrier -- and forms ZT planes of 4 x 64 outputs from
+// it, one row per wave, 32 voxels at a time, with the weights of its 32 output channels in registers.
+//
+// The sums are in the order of conv_ring_kernel, bitwise: the K-steps (tap pairs with 8 channels,
+// tap 2 k in lanes 0-31 and 2 k + 1 in the rest; taps with 16) fall into four chains of consecutive
+// steps, each summed from zero, and chain c of the tile w = 2 (y % 2) + x / 32 % 2 comes in the order
+// w, w - 1, w - 2, w - 3 modulo 4; the bias last.  With the order known per row parity and half, a
+// tile needs two accumulators.
+//
+// What bounds it is memory: 8 -> 32 on 1x256x64x64 moves 84 MB, 18 us at the rate of a large copy,
+// and takes 26 (FP32 result 31), where the ring kernel, whose waves pass partial sums to each other
+// for every 128 voxels, took 57; 16 -> 64 on 1x128x64x64 72 -> 42, 8 -> 32 on 128x32x32 17 -> 8 us.
+template <int CIN_, int ZT_>
+struct BoxConv {
+  static constexpr int CIN = CIN_, ZT = ZT_;
+  static constexpr int SEG = 64, ROWS = 4, NT = 256;
+  static constexpr int RV = SEG + 2, SR = ROWS + 2;  // staged voxels per row, rows per plane
+  static constexpr int VS = CIN == 8 ? 8 : CIN + 8;  // staged voxel stride: 4 x an odd number of dwords
+  static constexpr int Q = CIN / 8;                  // 16-byte chunks of a voxel
+  static constexpr int PLANE = SR * RV * VS;
+  static constexpr int CHUNKS = (ZT + 2) * SR * RV * Q;
+  static constexpr int PF = (CHUNKS + NT - 1) / NT;
+  static constexpr int KSTEPS = CIN == 8 ? 14 : 27;
+};
+
+template <typename P>
+__global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
+    const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
+    uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W, int cout, int relu) {
+  constexpr int Q = P::Q, CIN = P::CIN, VS = P::VS, RV = P::RV;
+  __shared__ __align__(16) uint16_t sv[(P::ZT + 2) * P::PLANE];
+  __shared__ __align__(16) float sb[32];
+  const int t = threadIdx.x, lane = t & 63, h = lane >> 5, c = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int co0 = blockIdx.y * 32;
+
+  // the blocks of one XCD (ids congruent modulo 8) take neighbouring boxes, which share halos
+  long long item = blockIdx.x;
+  if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
+  const int nseg = (W + P::SEG - 1) / P::SEG, nyb = (H + P::ROWS - 1) / P::ROWS, nzb = (D + P::ZT - 1) / P::ZT;
+  const int z0 = (int)(item % nzb) * P::ZT;
+  long long col = item / nzb;
+  const int x0 = (int)(col % nseg) * P::SEG;
+  col /= nseg;
+  const int y0 = (int)(col % nyb) * P::ROWS;
+  const long long nb = col / nyb;
+
+  uint4 pf[P::PF];
+#pragma unroll
+  for (int k = 0; k < P::PF; ++k) {
+    const int it = t + P::NT * k, q = it % Q, v = (it / Q) % RV, r = (it / (Q * RV)) % P::SR, pz = it / (Q * RV * P::SR);
+    const int x = x0 + v - 1, y = y0 + r - 1, z = z0 + pz - 1;
+    pf[k] = make_uint4(0, 0, 0, 0);
+    if (it < P::CHUNKS && x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D)
+      pf[k] = *reinterpret_cast<const uint4*>(in + (((nb * D + z) * H + y) * (long long)W + x) * CIN + 8 * q);
+  }
+  uint4 wb[P::KSTEPS];
+#pragma unroll
+  for (int k = 0; k < P::KSTEPS; ++k) {
+    wb[k] = make_uint4(0, 0, 0, 0);
+    const int tap = CIN == 8 ? 2 * k + h : k;
+    if (tap < 27)
+      wb[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + c) * CIN + (CIN == 8 ? 0 : 8 * h));
+  }
+  if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
+#pragma unroll
+  for (int k = 0; k < P::PF; ++k) {
+    const int it = t + P::NT * k, q = it % Q, v = it / Q;
+    if (it < P::CHUNKS) *reinterpret_cast<uint4*>(sv + v * VS + 8 * q) = pf[k];
+  }
+  __syncthreads();
+  const int y = y0 + wave;
+  if (y >= H) return;
+
+  // With 8 channels lanes 32-63 read the tap after that of lanes 0-31: the next voxel, or the
+  // first of the next row or plane (the zero weight of the last step reads tap 26 again).
+  const int b0 = (wave * RV + c) * VS + (CIN == 8 ? 0 : 8 * h);
+  const int b1 = CIN == 8 ? b0 + h * VS : b0, b2 = CIN == 8 ? b0 + h * (RV - 2) * VS : b0,
+            b3 = CIN == 8 ? b0 + h * (P::PLANE - (2 * RV + 2) * VS) : b0;
+  auto rows = [&](auto par) {  // par: y % 2
+#pragma unroll 1
+    for (int zz = 0; zz < P::ZT; ++zz) {
+      if (z0 + zz >= D) break;
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        if (x0 + 32 * half >= W) break;
+        const uint16_t* base = sv + zz * P::PLANE + half * 32 * VS;
+        floatx16 sum = {};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int ch = (2 * decltype(par)::value + half + 4 - j) % 4;
+          floatx16 chain = {};
+#pragma unroll
+          for (int k = P::KSTEPS * ch / 4; k < P::KSTEPS * (ch + 1) / 4; ++k) {
+            const int tap = CIN == 8 ? 2 * k : k, dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;  // each offset + 1
+            const int b = tap == 26 ? b0 : dx < 2 ? b1 : dy < 2 ? b2 : b3;
+            const uint4 vf = *reinterpret_cast<const uint4*>(base + b + dz * P::PLANE + (dy * RV + dx) * VS);
+            chain = mfma16(wb[k], vf, chain);
+          }
+          sum = j == 0 ? chain : sum + chain;
+        }
+        const int x = x0 + 32 * half + c;
+        uint2 u[4];
+        float f[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {  // channels 8 g + 4 h .. + 3
+          const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
+          const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            f[g][k] = sum[4 * g + k] + bb[k];
+            if (relu) f[g][k] = fmaxf(f[g][k], 0.0f);
+          }
+          u[g] = make_uint2(pack2(f[g][0], f[g][1]), pack2(f[g][2], f[g][3]));
+        }
+        const long long o = (((nb * D + z0 + zz) * H + y) * (long long)W + x) * cout + co0;
+        if (out_f32) {
+          if (x < W)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+              *reinterpret_cast<float4*>(out_f32 + o + 8 * g + 4 * h) = make_float4(f[g][0], f[g][1], f[g][2], f[g][3]);
+        } else {
+          // lanes 0-31 take groups 0 and 1 whole, lanes 32-63 groups 2 and 3
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            const auto px = __builtin_amdgcn_permlane32_swap(u[g].x, u[g + 2].x, false, false);
+            const auto py = __builtin_amdgcn_permlane32_swap(u[g].y, u[g + 2].y, false, false);
+            if (x < W) *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = make_uint4(px[0], py[0], px[1], py[1]);
+          }
+        }
+      }
+    }
+  };
+  if (wave & 1)
+    rows(std::integral_constant<int, 1>{});
+  else
+    rows(std::integral_constant<int, 0>{});
+}
+
+template <typename P>
+void launch_boxes(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32, int n, int d,
+                  int h, int wd, int cout, int relu, hipStream_t s) {
+  const long long items = (long long)n * ((d + P::ZT - 1) / P::ZT) * ((h + P::ROWS - 1) / P::ROWS) *
+                          ((wd + P::SEG - 1) / P::SEG);
+  hipLaunchKernelGGL(conv_box_kernel<P>, dim3((unsigned)items, cout / 32), dim3(P::NT), 0, s, in, w, bias, out, out_f32,
+                     d, h, wd, cout, relu);
+}
+
+// Boxes of two planes, or of one where those would leave compute units without a block (8 -> 64 on
+// 9x17x40, 50 boxes x 2: 6.3 against 7.5 us; 8 -> 32 on 256x64x64, 2048: 28.7 against 27.7; four
+// planes are no better there, and 68 against 45 us for three planes with 16 channels).
+template <int CIN>
+void launch_box(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32, int n, int d,
+                int h, int wd, int cout, int relu, hipStream_t s) {
+  if ((long long)n * ((d + 1) / 2) * ((h + 3) / 4) * ((wd + 63) / 64) * (cout / 32) > 256)
+    launch_boxes<BoxConv<CIN, 2>>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
+  else
+    launch_boxes<BoxConv<CIN, 1>>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
 }
 
 // w_t[tap'][ci][co] = w[26 - tap'][co][ci]
@@ -1432,12 +1594,20 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
                      (out_f32 ? aligned16(out_f32) : ((uintptr_t)out & 7) == 0) && ((uintptr_t)relu_y & 7) == 0;
   switch (cin) {
     case 8:
+      if (slide && (out_f32 || aligned16(out))) {
+        launch_box<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
+        return done();
+      }
       if (small_plane)
         launch_ring<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
         launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s);
       break;
     case 16:
+      if (slide && (out_f32 || aligned16(out))) {
+        launch_box<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
+        return done();
+      }
       if (small_plane)
         launch_ring<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else

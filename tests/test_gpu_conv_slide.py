@@ -1,6 +1,7 @@
-"""GPU test of the convolutions at the edges of the sliding kernel's tiles: volumes thinner than a
-tile or one voxel past it in every direction, one z plane up to several z ranges, volumes on both
-sides of the line above which 64 channels take the sliding kernel.  The reference is the FP64
+"""GPU test of the convolutions at the edges of the tiles of the sliding kernel (32 and 64 channels)
+and the box kernel (8 and 16): volumes thinner than a tile or one voxel past it in every
+direction, one z plane up to several z ranges, volumes on both sides of the lines above which 64
+channels take the sliding kernel and boxes have two planes.  The reference is the FP64
 convolution on the same BF16 values."""
 import numpy as np
 import pytest
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("cin", [8, 16, 32, 64])
 @pytest.mark.parametrize("n,d,h,w,cout", [(1, 1, 1, 1, 32), (1, 2, 9, 33, 32), (2, 3, 17, 31, 64), (1, 5, 8, 65, 32),
                                           (1, 40, 3, 5, 32), (1, 16, 15, 33, 32), (1, 17, 15, 33, 32),
-                                          (2, 9, 17, 31, 64)])
+                                          (2, 9, 17, 31, 64), (1, 33, 31, 65, 32)])
 def test_edges(cin, n, d, h, w, cout):
     import torch
     gen = torch.Generator().manual_seed(cin + 10 * d + w)
