@@ -533,6 +533,41 @@ void launch_staged(const uint16_t* in, const uint16_t* w, const float* bias, uin
                      cout, relu, ntiles);
 }
 
+// A wave's 32 x 32 result with channels as rows: lane (h, c) holds voxel c, register 4 g + k channel
+// 8 g + 4 h + k.
+__device__ __forceinline__ void add_bias_relu(floatx16& v, const float* sb, int h, int relu) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
+    const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float f = v[4 * g + k] + bb[k];
+      v[4 * g + k] = relu ? fmaxf(f, 0.0f) : f;
+    }
+  }
+}
+
+// As BF16 with 16 consecutive channels per lane, 16 h + 8 g of u[g]: the halves of the wave
+// exchange groups (v_permlane32_swap: the first operand's upper half and the second's lower half
+// change places), so that a lane stores 16 bytes at a time.
+__device__ __forceinline__ void pack_halves(const floatx16& v, uint4 (&u)[2]) {
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const auto x = __builtin_amdgcn_permlane32_swap(pack2(v[4 * g], v[4 * g + 1]), pack2(v[4 * g + 8], v[4 * g + 9]),
+                                                    false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(pack2(v[4 * g + 2], v[4 * g + 3]),
+                                                    pack2(v[4 * g + 10], v[4 * g + 11]), false, false);
+    u[g] = make_uint4(x[0], y[0], x[1], y[1]);
+  }
+}
+
+__device__ __forceinline__ void store_f32x16(float* o, const floatx16& v, int h) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<float4*>(o + 8 * g + 4 * h) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+}
+
 // ---------------------------------------------------------------- convolution, sliding
 // For cin in {32, 64}: activations, FP32 results and data gradients.  A block of eight waves owns a
 // co tile of 32, a tile of ROWS x SEG output columns and a range of z, and sweeps the input planes of
@@ -553,17 +588,17 @@ void launch_staged(const uint16_t* in, const uint16_t* w, const float* bias, uin
 // The weights of the co tile stay in LDS in fragment order (1 KB per tap and 16 channels, read
 // without conflicts); the plane of voxels has a voxel stride of CIN + 8 elements (4 x an odd number
 // of dwords, so that groups of 8 lanes reading 16 bytes cover all banks once).  The weights are the
-// first operand, so a lane holds 4 x 4 consecutive output channels of one voxel and stores 8 bytes
-// (16 in FP32) at a time; a data gradient's ReLU mask is applied there.  The next plane's global
+// first operand, so a lane holds 4 x 4 consecutive output channels of one voxel, and stores 16 bytes
+// at a time (in BF16 after an exchange between the halves of the wave); a data gradient's ReLU mask
+// is applied there.  The next plane's global
 // loads are issued before the MFMAs of the present one.
 //
 // What bounds it is the rate the card sustains on the matrix cores: an 8192^3 BF16 product reaches
 // 1180 TFLOP/s, a form of this kernel without its stores 1160.  Measured against the ring and
-// staged kernels (and their separate mask pass): 32 -> 32 on 1x256x64x64 105 -> 64 us (901 TFLOP/s),
-// FP32 result 98 -> 75, masked data gradient 125 -> 93; 1x128x32x32: 32 -> 64 51 -> 22 us, 64 -> 32
-// 64 -> 24; 64 -> 64 on 1x64x16x16 31 -> 17 us.  Two rows per wave with one accumulator per output (the
-// taps in any order) took 64 us for the first and 86 for the masked gradient; four rows in four
-// waves 85 us.
+// staged kernels (and their separate mask pass): 32 -> 32 on 1x256x64x64 97 -> 58 us (1000 TFLOP/s),
+// FP32 result 95 -> 64, masked data gradient 123 -> 70; 1x128x32x32: 32 -> 64 49 -> 20 us, 64 -> 32
+// 63 -> 21; 64 -> 64 on 1x64x16x16 31 -> 15 us.  With 8-byte stores (no exchange between the halves)
+// the first three took 62, 65 and 81 us.
 //
 // CIN: input channels; XT x WY waves, each 32 voxels of a row; NBUF staged planes (two where they
 // fit beside the weights: one barrier per plane instead of two).
@@ -718,15 +753,15 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
     }
     const int x = x0 + xt * 32 + c, y = y0 + wy;
     const bool put = p > za && y < H && x < W;  // output plane p - 1 is complete
-    const long long o = (((nb * D + p - 1) * H + y) * (long long)W + x) * cout + co0 + 4 * h;
-    uint2 m[4];
+    const long long o = (((nb * D + p - 1) * H + y) * (long long)W + x) * cout + co0;
+    uint4 m[2];
     if (MASKED && put) {  // in flight while the next plane goes to LDS
 #pragma unroll
-      for (int g = 0; g < 4; ++g) m[g] = *reinterpret_cast<const uint2*>(relu_y + o + 8 * g);
+      for (int g = 0; g < 2; ++g) m[g] = *reinterpret_cast<const uint4*>(relu_y + o + 16 * h + 8 * g);
     }
     if constexpr (P::NBUF == 1) __syncthreads();  // every wave is done with the plane
     if (more) store(p + 1);
-    if (put) {
+    if (p > za && y < H) {  // (uniform over the wave)
       floatx16 v;
       if constexpr (NA == 2) {
         v = acc[2][0] + acc[2][1];
@@ -738,23 +773,23 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
         else
           v = half ? ((c3 + c2) + c1) + c0 : ((c2 + c1) + c0) + c3;
       }
+      add_bias_relu(v, sb, h, relu);
+      if (out_f32) {
+        if (put) store_f32x16(out_f32 + o, v, h);
+      } else {
+        uint4 u[2];
+        pack_halves(v, u);
+        if (put)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {  // channels 8 g + 4 h .. + 3
-        const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
-        float f[4] = {v[4 * g + 0] + b4.x, v[4 * g + 1] + b4.y, v[4 * g + 2] + b4.z, v[4 * g + 3] + b4.w};
-        if (relu)
-#pragma unroll
-          for (int k = 0; k < 4; ++k) f[k] = fmaxf(f[k], 0.0f);
-        if (out_f32) {
-          *reinterpret_cast<float4*>(out_f32 + o + 8 * g) = make_float4(f[0], f[1], f[2], f[3]);
-        } else {
-          uint2 u = make_uint2(pack2(f[0], f[1]), pack2(f[2], f[3]));
-          if (MASKED) {  // the gradient of the pre-activation: 0 where the ReLU output is not positive
-            u.x &= positive_mask(m[g].x);
-            u.y &= positive_mask(m[g].y);
+          for (int g = 0; g < 2; ++g) {
+            if (MASKED) {  // the gradient of the pre-activation: 0 where the ReLU output is not positive
+              u[g].x &= positive_mask(m[g].x);
+              u[g].y &= positive_mask(m[g].y);
+              u[g].z &= positive_mask(m[g].z);
+              u[g].w &= positive_mask(m[g].w);
+            }
+            *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = u[g];
           }
-          *reinterpret_cast<uint2*>(out + o + 8 * g) = u;
-        }
       }
     }
 #pragma unroll
@@ -912,33 +947,16 @@ __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
           sum = j == 0 ? chain : sum + chain;
         }
         const int x = x0 + 32 * half + c;
-        uint2 u[4];
-        float f[4][4];
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {  // channels 8 g + 4 h .. + 3
-          const float4 b4 = *reinterpret_cast<const float4*>(sb + 8 * g + 4 * h);
-          const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            f[g][k] = sum[4 * g + k] + bb[k];
-            if (relu) f[g][k] = fmaxf(f[g][k], 0.0f);
-          }
-          u[g] = make_uint2(pack2(f[g][0], f[g][1]), pack2(f[g][2], f[g][3]));
-        }
+        add_bias_relu(sum, sb, h, relu);
         const long long o = (((nb * D + z0 + zz) * H + y) * (long long)W + x) * cout + co0;
         if (out_f32) {
+          if (x < W) store_f32x16(out_f32 + o, sum, h);
+        } else {
+          uint4 u[2];
+          pack_halves(sum, u);
           if (x < W)
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-              *reinterpret_cast<float4*>(out_f32 + o + 8 * g + 4 * h) = make_float4(f[g][0], f[g][1], f[g][2], f[g][3]);
-        } else {
-          // lanes 0-31 take groups 0 and 1 whole, lanes 32-63 groups 2 and 3
-#pragma unroll
-          for (int g = 0; g < 2; ++g) {
-            const auto px = __builtin_amdgcn_permlane32_swap(u[g].x, u[g + 2].x, false, false);
-            const auto py = __builtin_amdgcn_permlane32_swap(u[g].y, u[g + 2].y, false, false);
-            if (x < W) *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = make_uint4(px[0], py[0], px[1], py[1]);
-          }
+            for (int g = 0; g < 2; ++g) *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = u[g];
         }
       }
     }
@@ -1589,12 +1607,12 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
   const long long nvox = (long long)n * d * h * wd;
   hipStream_t s = S(stream);
   const bool small_plane = (long long)h * wd * cin < (1LL << 31);  // 32-bit offsets within an input plane
-  // the sliding kernel moves 16 bytes at a time, and 8 of its BF16 output and mask
+  // the sliding and the box kernel move 16 bytes at a time
   const bool slide = small_plane && aligned16(in) && aligned16(w) &&
-                     (out_f32 ? aligned16(out_f32) : ((uintptr_t)out & 7) == 0) && ((uintptr_t)relu_y & 7) == 0;
+                     (out_f32 ? aligned16(out_f32) : aligned16(out)) && ((uintptr_t)relu_y & 15) == 0;
   switch (cin) {
     case 8:
-      if (slide && (out_f32 || aligned16(out))) {
+      if (slide) {
         launch_box<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
         return done();
       }
@@ -1604,7 +1622,7 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
         launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s);
       break;
     case 16:
-      if (slide && (out_f32 || aligned16(out))) {
+      if (slide) {
         launch_box<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
         return done();
       }
