@@ -325,11 +325,11 @@ extern "C" lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_r, const dou
 // Planes per workgroup of tx x ty tiles when none is set: the number of z chunks that minimises
 // (rounds of resident workgroups) x (planes per chunk + the 2 planes each chunk pulls first);
 // *cost is that product.
-// Between lateral walls the tiles along them take longer per plane, so in a long chunk their neighbours
-// run ahead, until halo rows have left L2 when the other tile needs them; the next chunk starts
-// them together again.  In FP32, where that traffic counts, chunks are at most kWallChunk planes if that
-// costs no more than 5 % by the measure above: the jet 256x256x1024 between walls 4.85 ms against 5.49
-// with 512 planes, 256x256x512 2.46 against 2.64 (FP16 4.11 against 4.04, 2.07 against 2.01).
+// Between lateral walls the tiles along them take longer per plane than the others, and one round of
+// long chunks lasts as long as its slowest; with shorter ones the compute units that are done early take
+// more of them.  In FP32 chunks are at most kWallChunk planes if that costs no more than 5 % by the
+// measure above: the jet 256x256x1024 between walls 4.85 ms against 5.49 with 512 planes, 256x256x512
+// 2.46 against 2.64 (FP16 4.11 against 4.04, 2.07 against 2.01).
 static constexpr int kWallChunk = 64;
 static int auto_zchunk(const lbm_ctx* c, int tx, int ty, long long* cost = nullptr) {
   const Geo& G = c->geo;
