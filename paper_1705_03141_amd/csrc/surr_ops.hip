@@ -1612,21 +1612,17 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
                      (out_f32 ? aligned16(out_f32) : aligned16(out)) && ((uintptr_t)relu_y & 15) == 0;
   switch (cin) {
     case 8:
-      if (slide) {
+      if (slide)  // (the box kernel applies no mask: the pass below does)
         launch_box<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-        return done();
-      }
-      if (small_plane)
+      else if (small_plane)
         launch_ring<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
         launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s);
       break;
     case 16:
-      if (slide) {
+      if (slide)  // (the box kernel applies no mask: the pass below does)
         launch_box<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-        return done();
-      }
-      if (small_plane)
+      else if (small_plane)
         launch_ring<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       else
         launch_staged<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
