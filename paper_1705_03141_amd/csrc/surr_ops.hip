@@ -625,7 +625,7 @@ template <typename P, bool MASKED>
 __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
     const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
     const uint16_t* __restrict__ relu_y, uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W,
-    int cout, int relu, int nzc, int zlen) {
+    int cout, int relu, int nzc, int zlen, long long item0) {
   constexpr int SL = P::SL, Q = P::Q;
   __shared__ __align__(16) uint16_t sw[P::WELEMS];
   __shared__ __align__(16) uint16_t sv[P::NBUF * P::PLANE];
@@ -637,6 +637,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
   // the blocks of one XCD (ids congruent modulo 8) take neighbouring items, which share halos
   long long item = blockIdx.x;
   if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
+  item += item0;
   const int nseg = (W + P::SEG - 1) / P::SEG, nyb = (H + P::ROWS - 1) / P::ROWS;
   const int zc = (int)(item % nzc);
   long long col = item / nzc;
@@ -801,6 +802,10 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
   }
 }
 
+// Blocks of one launch of the kernels that take one item a block, along x: a launch may hold less than
+// 2^32 threads along it, and 512 x 2^22 do (many volumes of one voxel have an item each).
+constexpr long long kMaxItems = 1LL << 22;
+
 template <typename P>
 void launch_slide(const uint16_t* in, const uint16_t* w, const float* bias, const uint16_t* relu_y, uint16_t* out,
                   float* out_f32, int n, int d, int h, int wd, int cout, int relu, hipStream_t s) {
@@ -821,13 +826,15 @@ void launch_slide(const uint16_t* in, const uint16_t* w, const float* bias, cons
   }
   const int zlen = (d + nzc - 1) / nzc;
   const long long nitems = ncols * nzc;
-  const dim3 grid((unsigned)nitems, ctiles), block(P::NT);
-  if (relu_y)
-    hipLaunchKernelGGL((conv_slide_kernel<P, true>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
-                       cout, relu, nzc, zlen);
-  else
-    hipLaunchKernelGGL((conv_slide_kernel<P, false>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
-                       cout, relu, nzc, zlen);
+  for (long long i = 0; i < nitems; i += kMaxItems) {
+    const dim3 grid((unsigned)(nitems - i < kMaxItems ? nitems - i : kMaxItems), ctiles), block(P::NT);
+    if (relu_y)
+      hipLaunchKernelGGL((conv_slide_kernel<P, true>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
+                         cout, relu, nzc, zlen, i);
+    else
+      hipLaunchKernelGGL((conv_slide_kernel<P, false>), grid, block, 0, s, in, w, bias, relu_y, out, out_f32, d, h, wd,
+                         cout, relu, nzc, zlen, i);
+  }
 }
 
 // 32 channels: tiles of 4 rows x 64 voxels or 8 rows x 32, whichever covers the plane with less
@@ -873,7 +880,7 @@ struct BoxConv {
 template <typename P>
 __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
     const uint16_t* __restrict__ in, const uint16_t* __restrict__ w, const float* __restrict__ bias,
-    uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W, int cout, int relu) {
+    uint16_t* __restrict__ out, float* __restrict__ out_f32, int D, int H, int W, int cout, int relu, long long item0) {
   constexpr int Q = P::Q, CIN = P::CIN, VS = P::VS, RV = P::RV;
   __shared__ __align__(16) uint16_t sv[(P::ZT + 2) * P::PLANE];
   __shared__ __align__(16) float sb[32];
@@ -884,6 +891,7 @@ __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
   // the blocks of one XCD (ids congruent modulo 8) take neighbouring boxes, which share halos
   long long item = blockIdx.x;
   if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
+  item += item0;
   const int nseg = (W + P::SEG - 1) / P::SEG, nyb = (H + P::ROWS - 1) / P::ROWS, nzb = (D + P::ZT - 1) / P::ZT;
   const int z0 = (int)(item % nzb) * P::ZT;
   long long col = item / nzb;
@@ -972,8 +980,9 @@ void launch_boxes(const uint16_t* in, const uint16_t* w, const float* bias, uint
                   int h, int wd, int cout, int relu, hipStream_t s) {
   const long long items = (long long)n * ((d + P::ZT - 1) / P::ZT) * ((h + P::ROWS - 1) / P::ROWS) *
                           ((wd + P::SEG - 1) / P::SEG);
-  hipLaunchKernelGGL(conv_box_kernel<P>, dim3((unsigned)items, cout / 32), dim3(P::NT), 0, s, in, w, bias, out, out_f32,
-                     d, h, wd, cout, relu);
+  for (long long i = 0; i < items; i += kMaxItems)
+    hipLaunchKernelGGL(conv_box_kernel<P>, dim3((unsigned)(items - i < kMaxItems ? items - i : kMaxItems), cout / 32),
+                       dim3(P::NT), 0, s, in, w, bias, out, out_f32, d, h, wd, cout, relu, i);
 }
 
 // Boxes of two planes, or of one where those would leave compute units without a block (8 -> 64 on
