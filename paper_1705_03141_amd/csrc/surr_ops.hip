@@ -812,14 +812,19 @@ void launch_slide(const uint16_t* in, const uint16_t* w, const float* bias, cons
   const int ctiles = cout / 32;
   const long long ncols = (long long)n * ((h + P::ROWS - 1) / P::ROWS) * ((wd + P::SEG - 1) / P::SEG);
   // One block fills a compute unit's LDS: the number of z ranges that minimises the rounds of 256
-  // blocks times the planes of a block, its halo and its start-up (about 1.5 planes) included.
+  // blocks times the planes of a block, its halo and its start-up (about 1.5 planes) included, here
+  // in half planes.  k ranges cost at least (2 d + 3 k) c / 256, which grows with k: the search ends
+  // where that reaches the best so far (at k = 17 of 256 for 1x256x64x64; over every k it cost the host
+  // 1.4 us a call there and 22 us with d = 4096).
   int nzc = 1;
-  double best = -1.0;
+  long long best = -1;
+  const long long c = ncols * ctiles;
   for (int k = 1; k <= d; ++k) {
+    if (best >= 0 && c * (2LL * d + 3LL * k) >= 256 * best) break;
     const int zl = (d + k - 1) / k;
     if ((d + zl - 1) / zl != k) continue;
-    const double cost = (double)((ncols * k * ctiles + 255) / 256) * (zl + 1.5);
-    if (best < 0.0 || cost < best) {
+    const long long cost = (c * k + 255) / 256 * (2LL * zl + 3);
+    if (best < 0 || cost < best) {
       best = cost;
       nzc = k;
     }

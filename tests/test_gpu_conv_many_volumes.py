@@ -23,3 +23,23 @@ def test_many_volumes(cin, n):
     got = y.view(torch.bfloat16).double()
     # one BF16 rounding on top of an FP32 sum of cin products of magnitude about 1
     assert bool(((got - want).abs() <= want.abs() * 2.0 ** -8 + 1e-4).all())
+
+
+def test_long_volume_is_enqueued_at_once():
+    """The host's part of a call does not grow with the number of planes: 2^22 planes, for which a
+    search over every split into ranges takes over 20 ms."""
+    import time
+
+    import torch
+    d, c = 2 ** 22, 32
+    x = torch.zeros((d, c), dtype=torch.int16, device="cuda")
+    wt = torch.zeros((27, c, c), dtype=torch.int16, device="cuda")
+    y = torch.empty_like(x)
+    host = []
+    for _ in range(4):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        assert S._lib().surr_conv3d_fwd(S._p(x), S._p(wt), None, S._p(y), None, 1, d, 1, 1, c, c, 0, None) == 0
+        host.append(time.perf_counter() - t)
+    torch.cuda.synchronize()
+    assert min(host) < 5e-3
