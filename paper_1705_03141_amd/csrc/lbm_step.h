@@ -192,7 +192,8 @@ __device__ __forceinline__ float div_nc(float a, float b) {
 // Complete a pull whose population loads are in ld, with the staged scalars of the three source
 // planes in S and W (row stride SX; idx0 is the cell's corner (-1, -1)).  GROUP > 0 keeps the
 // LDS reads of at most that many directions in flight, for callers with few registers.
-template <typename T, int MODE, bool WANT_DF, int SX, int GROUP = 0>
+// UNSCALE_LAST: the deviations leave the storage scale together at the end, not one by one.
+template <typename T, int MODE, bool WANT_DF, int SX, int GROUP = 0, bool UNSCALE_LAST = false>
 __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], const float4* const (&S)[3], const float2* const (&W)[3],
                                             int idx0, const PullConst& C, float& rho, float& rho_r, float& rho_b,
                                             float& e_new, float (&df)[Q], float& shift_out, float& drho_out) {
@@ -214,7 +215,8 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
   // depend on the tiling.
   float d_rho = Word<T>::dec_scaled(ld[0]);
   float d_t = mul_nc(t_self, d_rho);
-  if constexpr (WANT_DF) df[0] = SC == 1.0f ? d_rho : mul_nc(d_rho, 1.0f / SC);
+  constexpr bool kScaleAtOnce = SC != 1.0f && !UNSCALE_LAST;
+  if constexpr (WANT_DF) df[0] = kScaleAtOnce ? mul_nc(d_rho, 1.0f / SC) : d_rho;
   static_for<1, Q>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     constexpr Src s = resolve<i, MODE>();
@@ -240,14 +242,15 @@ __device__ __forceinline__ void finish_pull(const typename Word<T>::W (&ld)[Q], 
     }
     d_rho = add_nc(d_rho, d);
     d_t = add_nc(d_t, inc);
-    // (unscaled here, not in a loop over df afterwards: that one kept both forms of the 27 values
-    // live, and the FP16 instance at 256 VGPRs instead of 208)
-    if constexpr (WANT_DF) df[i] = SC == 1.0f ? d : mul_nc(d, 1.0f / SC);
+    if constexpr (WANT_DF) df[i] = kScaleAtOnce ? mul_nc(d, 1.0f / SC) : d;
     if constexpr (GROUP > 0 && i % (GROUP > 0 ? GROUP : 1) == 0) __builtin_amdgcn_sched_barrier(0);
   });
   if constexpr (SC != 1.0f) {
     d_rho = mul_nc(d_rho, 1.0f / SC);
     d_t = mul_nc(d_t, 1.0f / SC);
+    if constexpr (WANT_DF && UNSCALE_LAST)
+#pragma unroll
+      for (int i = 0; i < Q; ++i) df[i] = mul_nc(df[i], 1.0f / SC);
   }
   rho = add_nc(rho_old, d_rho);
   const float rho_t = fmaf(t_self, rho_old, d_t), rho_o = sub_nc(rho, rho_t);
@@ -304,10 +307,10 @@ struct PlaneState {
   }
 };
 
-template <typename T, int TX, int TY, bool INIT, bool WALLS>
 #ifndef LBM_STEP_WAVES_PER_EU
 #define LBM_STEP_WAVES_PER_EU 2
 #endif
+template <typename T, int TX, int TY, bool INIT, bool WALLS, bool BATCH>
 __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb) {
   using Tile = StepTile<TX, TY>;
   constexpr int NT = Tile::kThreads, NR = Tile::kRing, SX = Tile::SX, NS = Tile::kStaged, DX = Tile::DX,
@@ -318,14 +321,25 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // the collision (their slot held p-3, last read two barriers earlier).
   __shared__ float4 sS[4][NS];  // staged scalars (e, a, b, w_x) of source planes
   __shared__ float2 sW[4][NS];  // (w_y, w_z)
+  // The form for single FP16 lattices without lateral walls.  The deviations leave the storage scale in a
+  // loop at the end of the pull, which leaves the scheduler free to keep the 27 values in flight: the
+  // instance takes all 256 VGPRs, and every register it can do without counts, because a spilled one
+  // is reloaded behind all outstanding loads (jet 256x256x512, ms per step: 1.82 without a spill, 1.91
+  // with one, 1.97 with four; 1.87 in the form of the other instances, which takes 208).  Hence the one
+  // staging buffer for all passes, filled plane by plane at the start, z wrapped by a division (on the
+  // scalar unit), the column and the staging address formed where they are used, and the pairs of the
+  // density ring interleaved.
+  // In a batch, whose arguments lie in memory, the other form is the faster (six jets of 96 to 112
+  // cells 1.90 against 1.92); between walls, and in tiles of 128 cells, it spills.
+  constexpr bool kWide = std::is_same<T, _Float16>::value && !WALLS && !BATCH && TX * TY >= 256;
   // Density ring of time t with a 1-cell ring, 4 slots: per cell the pairs (rho_r/rho, rho)
   // (sel 0) and (rho_b/rho, rho) (sel 1), so that a reader takes its minority colour's fraction
   // and rho with one 8-byte read.  The two pairs lie in separate arrays of 4 slots each, where
   // a wave's reads of neighbouring cells fall on distinct banks (against pairs interleaved per
-  // cell, on the jet: +1.3 % FP32, +5 % FP16).
+  // cell, on the jet: +1.3 % FP32; the form above has no register for it).
   __shared__ float2 sDf[8 * ND];
   // index of pair sel of cell d in slot s
-  auto dat = [](int s, int sel, int d) { return (sel * 4 + s) * ND + d; };
+  auto dat = [](int s, int sel, int d) { return kWide ? s * 2 * ND + 2 * d + sel : (sel * 4 + s) * ND + d; };
   auto slot4 = [](int q) { return q & 3; };
   // Issue order of a pass's loads (measured): with FP32 populations the staged scalars go
   // first, with 16-bit populations after the population loads.  Their LDS write waits until
@@ -405,6 +419,10 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // pass into pieces that are scheduled apart (FP16 jet 3.71 ms with them, 3.68 without)
   auto zwrap = [&](int q) {
     const int n = G.nz;
+    if constexpr (kWide) {
+      q = q % n;
+      return q < 0 ? q + n : q;
+    }
     q = q < 0 ? q + n : q;
     q = q < 0 ? q + n : q;
     q = q >= n ? q - n : q;
@@ -424,6 +442,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   };
   auto stage_store = [&](int q, const float(&st)[KS][5]) {
     const int s = slot4(q);
+    int at = tid;
+    if constexpr (kWide) asm volatile("" : "+v"(at));  // not one LDS address per array across the loop
     int sign = walls;
     if constexpr (WALLS) asm volatile("" : "+v"(sign));  // not one mask per staged cell across the loop
 #pragma unroll
@@ -435,8 +455,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
           wx = __uint_as_float(__float_as_uint(wx) ^ (((unsigned)sign << (23 - 2 * k)) & 0x80000000u));
           wy = __uint_as_float(__float_as_uint(wy) ^ (((unsigned)sign << (22 - 2 * k)) & 0x80000000u));
         }
-        sS[s][tid + k * NT] = make_float4(st[k][0], psi_a(psi), psi_b(psi), wx);
-        sW[s][tid + k * NT] = make_float2(wy, st[k][4]);
+        sS[s][at + k * NT] = make_float4(st[k][0], psi_a(psi), psi_b(psi), wx);
+        sW[s][at + k * NT] = make_float2(wy, st[k][4]);
       }
   };
 
@@ -445,7 +465,14 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   bufB.clear();
   bool bad = false;  // a collided cell had a NaN, infinite or non-positive density
 
-  if constexpr (!INIT) {
+  float st_all[KS][5];  // (kWide)
+  if constexpr (!INIT && kWide) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      stage_load(z0 - 2 + k, st_all);
+      stage_store(z0 - 2 + k, st_all);
+    }
+  } else if constexpr (!INIT) {
     float st[3][KS][5];  // the first three planes in one go
 #pragma unroll
     for (int k = 0; k < 3; ++k) stage_load(z0 - 2 + k, st[k]);
@@ -468,7 +495,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     // that its loads go out, and the barrier is reached, sooner.
     __builtin_amdgcn_s_setprio(1);
     // 1. the loads of the scalars of plane p+3 and of the populations of plane p+1
-    float st[KS][5];
+    float st_one[KS][5];
+    float(&st)[KS][5] = kWide ? st_all : st_one;
     if constexpr (!INIT && kStageFirst) stage_load(p + 3, st);
     __builtin_amdgcn_sched_barrier(0);
     typename Word<T>::W ldI[Q], ldR[Q];
@@ -552,8 +580,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
         nxt.shift = nxt.drho = 0.0f;
       } else {
         with_mode(mode, [&](auto M) {
-          finish_pull<T, decltype(M)::value, true, SX>(ldI, S, W, bI, A.pc, nxt.rho, nxt.rho_r, nxt.rho_b, nxt.e,
-                                                       nxt.df, nxt.shift, nxt.drho);
+          finish_pull<T, decltype(M)::value, true, SX, 0, kWide>(ldI, S, W, bI, A.pc, nxt.rho, nxt.rho_r, nxt.rho_b,
+                                                                 nxt.e, nxt.df, nxt.shift, nxt.drho);
         });
       }
       if (is_inflow(G, gx, gy, zq)) {  // R10: inflow sites are pure red at rho_r0
@@ -576,6 +604,13 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
     if (p >= z0 && live) {
       const rsrc_t gslab = buffer_of(gout + (size_t)p * slab_bytes, slab_bytes);
       const rsrc_t sslab = buffer_of(A.sc_out + (size_t)p * 5 * (size_t)plane, sc_bytes);
+      int oc = col;
+      if constexpr (kWide) {
+        int ox = gx, oy = gy;
+        asm volatile("" : "+v"(ox), "+v"(oy));
+        oc = oy * G.nx + ox;
+      }
+      const unsigned atT = kWide ? (unsigned)(oc * (int)sizeof(T)) : colT, at4 = kWide ? (unsigned)(oc * 4) : col4;
       // (inflow sites are collided like any cell here; inflow_kernel overwrites them)
       {
         const int sm = (!zper && p == 0) ? slot4(p) : slot4(p - 1);
@@ -603,7 +638,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
             for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
               for (int dx = 0; dx < 3; ++dx) {
-                const float2 v = D2[slots[dz] * ND + b0 + yo[dy] + xo[dx]];
+                const float2 v = D2[dat(slots[dz], 0, b0 + yo[dy] + xo[dx])];
                 vp[dz][dy][dx] = v.x;
                 vr[dz][dy][dx] = v.y;
               }
@@ -623,12 +658,12 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
         collide_cell<Word<T>::kOutShift>(A.cp, A.rates, cur.df, cur.shift, cur.drho, cur.rho, cur.rho_r, cur.rho_b, gp,
                                          gr, o);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) Word<T>::store(Word<T>::enc_scaled(o.g[i]), gslab, colT, i * pb);
-        store_f32(cur.e, sslab, col4, 0);
-        store_f32(psi_encode(cur.rho_r, cur.rho_b, cur.rho), sslab, col4, plane * 4);
-        store_f32(o.wx, sslab, col4, 2 * plane * 4);
-        store_f32(o.wy, sslab, col4, 3 * plane * 4);
-        store_f32(o.wz, sslab, col4, 4 * plane * 4);
+        for (int i = 0; i < Q; ++i) Word<T>::store(Word<T>::enc_scaled(o.g[i]), gslab, atT, i * pb);
+        store_f32(cur.e, sslab, at4, 0);
+        store_f32(psi_encode(cur.rho_r, cur.rho_b, cur.rho), sslab, at4, plane * 4);
+        store_f32(o.wx, sslab, at4, 2 * plane * 4);
+        store_f32(o.wy, sslab, at4, 3 * plane * 4);
+        store_f32(o.wz, sslab, at4, 4 * plane * 4);
       }
     }
   };
@@ -643,7 +678,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
 
 template <typename T, int TX, int TY, bool INIT, bool WALLS>
 __global__ void __launch_bounds__(TX * TY, LBM_STEP_WAVES_PER_EU) step_kernel(const StepArgs A) {
-  step_body<T, TX, TY, INIT, WALLS>(A, (int)blockIdx.x, (int)gridDim.x);
+  step_body<T, TX, TY, INIT, WALLS, false>(A, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // Many lattices in one launch: case c owns blocks [first[c], first[c+1]) of the grid, each
@@ -660,7 +695,7 @@ __global__ void __launch_bounds__(TX * TY, LBM_STEP_WAVES_PER_EU)
     else
       hi = mid;
   }
-  step_body<T, TX, TY, INIT, WALLS>(cases[lo], b - first[lo], first[lo + 1] - first[lo]);
+  step_body<T, TX, TY, INIT, WALLS, true>(cases[lo], b - first[lo], first[lo + 1] - first[lo]);
 }
 
 // Inflow sites (R10) after a step: each emits the red equilibrium at rho_r0 and u_in(1 + eps xi)
