@@ -321,17 +321,21 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // the collision (their slot held p-3, last read two barriers earlier).
   __shared__ float4 sS[4][NS];  // staged scalars (e, a, b, w_x) of source planes
   __shared__ float2 sW[4][NS];  // (w_y, w_z)
-  // The form for single FP16 lattices without lateral walls.  The deviations leave the storage scale in a
-  // loop at the end of the pull, which leaves the scheduler free to keep the 27 values in flight: the
-  // instance takes all 256 VGPRs, and every register it can do without counts, because a spilled one
-  // is reloaded behind all outstanding loads (jet 256x256x512, ms per step: 1.82 without a spill, 1.91
-  // with one, 1.97 with four; 1.87 in the form of the other instances, which takes 208).  Hence the one
-  // staging buffer for all passes, filled plane by plane at the start, z wrapped by a division (on the
-  // scalar unit), the column and the staging address formed where they are used, and the pairs of the
-  // density ring interleaved.
-  // In a batch, whose arguments lie in memory, the other form is the faster (six jets of 96 to 112
-  // cells 1.90 against 1.92); between walls, and in tiles of 128 cells, it spills.
+  // A spilled register is reloaded behind all outstanding loads, and one of them costs about 5 % of a
+  // step.  The instances that take all 256 registers do without those they can (kSparing): z and the
+  // cell's coordinates wrapped by divisions, the column and the staging address formed where they are
+  // used.  BF16 batches, six lattices 64x64x128: 271 us per step with six spilled registers, 259 with
+  // two, 254 without.
+  //
+  // kWide: single FP16 lattices without lateral walls.  The deviations leave the storage scale in a loop
+  // at the end of the pull, which leaves the scheduler free to keep the 27 values in flight; one staging
+  // buffer serves all passes, filled plane by plane at the start, and the pairs of the density ring are
+  // interleaved.  Jet 256x256x512, ms per step: 1.82 so, 1.91 with one spilled register, 1.97 with
+  // four; 1.87 in the form of the other instances, which takes 208 registers.  In a batch, whose
+  // arguments lie in memory, the other form is the faster (six jets of 96 to 112 cells 1.90 against
+  // 1.92); between walls, and in tiles of 128 cells, this one spills.
   constexpr bool kWide = std::is_same<T, _Float16>::value && !WALLS && !BATCH && TX * TY >= 256;
+  constexpr bool kSparing = kWide || (std::is_same<T, bf16>::value && !WALLS && BATCH);
   // Density ring of time t with a 1-cell ring, 4 slots: per cell the pairs (rho_r/rho, rho)
   // (sel 0) and (rho_b/rho, rho) (sel 1), so that a reader takes its minority colour's fraction
   // and rho with one 8-byte read.  The two pairs lie in separate arrays of 4 slots each, where
@@ -373,7 +377,12 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // own cell
   const int tid = threadIdx.x;
   const int lx = tid % TX, ly = tid / TX;
-  const int gx = wrap(x0 + lx, G.nx), gy = wrap(y0 + ly, G.ny);
+  auto wrapped = [](int v, int n) {
+    if constexpr (!kSparing) return wrap(v, n);
+    v = v % n;
+    return v < 0 ? v + n : v;
+  };
+  const int gx = wrapped(x0 + lx, G.nx), gy = wrapped(y0 + ly, G.ny);
   const bool live = (x0 + lx < G.nx) && (y0 + ly < G.ny);
   const int col = gy * G.nx + gx;
   const int sI = (ly + 2) * SX + lx + 2, dI = (ly + 1) * DX + lx + 1;
@@ -381,7 +390,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   const bool ringer = tid < NR;
   int rx = 0, ry = 0;
   if (ringer) ring_cell<TX, TY>(tid, rx, ry);
-  const int rgx = wrap(x0 + rx, G.nx), rgy = wrap(y0 + ry, G.ny);
+  const int rgx = wrapped(x0 + rx, G.nx), rgy = wrapped(y0 + ry, G.ny);
   const int rcol = rgy * G.nx + rgx;
   const int sR = (ry + 2) * SX + rx + 2, dR = (ry + 1) * DX + rx + 1;
   // Lateral walls: the wall flags of the own and the ring cell, and whether the tile has any
@@ -403,13 +412,13 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
       sx = mirror(ux, G.nx);
       if (ux < 0 || ux >= G.nx) walls |= 256 << (2 * k);
     } else {
-      sx = wrap(ux, G.nx);
+      sx = wrapped(ux, G.nx);
     }
     if (WALLS && G.wall_y) {
       sy = mirror(uy, G.ny);
       if (uy < 0 || uy >= G.ny) walls |= 512 << (2 * k);
     } else {
-      sy = wrap(uy, G.ny);
+      sy = wrapped(uy, G.ny);
     }
     stOff[k] = (unsigned)((sy * G.nx + sx) * 4);
   }
@@ -419,7 +428,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   // pass into pieces that are scheduled apart (FP16 jet 3.71 ms with them, 3.68 without)
   auto zwrap = [&](int q) {
     const int n = G.nz;
-    if constexpr (kWide) {
+    if constexpr (kSparing) {
       q = q % n;
       return q < 0 ? q + n : q;
     }
@@ -443,7 +452,7 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   auto stage_store = [&](int q, const float(&st)[KS][5]) {
     const int s = slot4(q);
     int at = tid;
-    if constexpr (kWide) asm volatile("" : "+v"(at));  // not one LDS address per array across the loop
+    if constexpr (kSparing) asm volatile("" : "+v"(at));  // not one LDS address per array across the loop
     int sign = walls;
     if constexpr (WALLS) asm volatile("" : "+v"(sign));  // not one mask per staged cell across the loop
 #pragma unroll
@@ -605,12 +614,12 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
       const rsrc_t gslab = buffer_of(gout + (size_t)p * slab_bytes, slab_bytes);
       const rsrc_t sslab = buffer_of(A.sc_out + (size_t)p * 5 * (size_t)plane, sc_bytes);
       int oc = col;
-      if constexpr (kWide) {
+      if constexpr (kSparing) {
         int ox = gx, oy = gy;
         asm volatile("" : "+v"(ox), "+v"(oy));
         oc = oy * G.nx + ox;
       }
-      const unsigned atT = kWide ? (unsigned)(oc * (int)sizeof(T)) : colT, at4 = kWide ? (unsigned)(oc * 4) : col4;
+      const unsigned atT = kSparing ? (unsigned)(oc * (int)sizeof(T)) : colT, at4 = kSparing ? (unsigned)(oc * 4) : col4;
       // (inflow sites are collided like any cell here; inflow_kernel overwrites them)
       {
         const int sm = (!zper && p == 0) ? slot4(p) : slot4(p - 1);
