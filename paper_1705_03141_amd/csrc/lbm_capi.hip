@@ -858,8 +858,7 @@ static lbm_status build_groups(lbm_batch* b) {
         h[par].push_back(s);
       }
       const StepArgs& s = h[0].back();
-      const long long blocks = (long long)s.tiles_x * s.tiles_y * s.nchunks;
-      first[j + 1] = first[j] + (int)((blocks + 7) / 8 * 8);
+      first[j + 1] = first[j] + (int)((step_blocks(s) + 7) / 8 * 8);
     }
     g.nblocks = first[n];
     bool ok = true;
@@ -1143,13 +1142,32 @@ extern "C" lbm_status lbm_selftest_tile_sets_host(const lbm_params* params, int 
   if (st != LBM_OK) return fail(nullptr, st, msg);
   tmp.tx = tx;
   tmp.ty = ty;
-  tmp.zchunk = tmp.geo.nz;
+  const bool walls = tmp.geo.wall_x || tmp.geo.wall_y;
   StepArgs s{};
-  fill_step_args(&tmp, 0, 0, s);
+  // the step's map from blocks to places, walked over the whole grid of a launch and of a batch's part
+  // (padded to a multiple of 8), with a chunk per plane, some and one; a count other than 1 is kept
+  std::vector<int> times, at;
+  for (const int zchunk : {1, 7, tmp.geo.nz})
+    for (const int pad : {1, 8}) {
+      tmp.zchunk = zchunk;
+      fill_step_args(&tmp, 0, 0, s);
+      const int tiles = s.tiles_x * s.tiles_y;
+      times.resize(tiles, 1);
+      const long long nb = (step_blocks(s) + pad - 1) / pad * pad;
+      if (zchunk < tmp.geo.nz && nb > (1ll << 24)) continue;
+      at.assign((size_t)tiles * s.nchunks, 0);
+      for (int L = 0; L < (int)nb; ++L) {
+        int chunk, tile;
+        place_of(s, L, (int)nb, chunk, tile);
+        if (chunk >= s.nchunks) continue;
+        if (chunk < 0 || tile < 0 || tile >= tiles) return fail(nullptr, LBM_EDEVICE, "a block outside of the lattice");
+        ++at[(size_t)chunk * tiles + tile];
+      }
+      for (size_t k = 0; k < at.size(); ++k)
+        if (at[k] != 1) times[k % tiles] = at[k];
+    }
   const int nt = s.tiles_x * s.tiles_y;
   for (int k = 0; k < 3 * nt; ++k) counts[k] = 0;
-  const bool walls = tmp.geo.wall_x || tmp.geo.wall_y;
-  // the step's block-to-tile map, tile by tile
   for (int t = 0; t < nt; ++t) {
     const int j = t / s.tiles_x, i = t - j * s.tiles_x;
     const int b = !walls ? 0 : (interior_tile(s, i, j) ? 1 : 2);
@@ -1159,7 +1177,7 @@ extern "C" lbm_status lbm_selftest_tile_sets_host(const lbm_params* params, int 
     const bool on_wall = (tmp.geo.wall_x && (x0 == 0 || x0 + tx > tmp.geo.nx - 2)) ||
                          (tmp.geo.wall_y && (y0 == 0 || y0 + ty > tmp.geo.ny - 2));
     if (b == 1 && on_wall) return fail(nullptr, LBM_EDEVICE, "a tile on a wall takes the plain loads");
-    counts[b * nt + t]++;
+    counts[b * nt + t] = times[t];
   }
   return LBM_OK;
 }

@@ -42,6 +42,19 @@ struct StepArgs {
   GroupRates rates;
 };
 
+// Blocks of a step's launch.
+inline long long step_blocks(const StepArgs& a) { return (long long)a.tiles_x * a.tiles_y * a.nchunks; }
+
+// Block L of the nb blocks of a lattice (its launch, or its part of a batch's) -> z chunk and tile; a chunk
+// from nchunks on is a block of padding.  The hardware sends blocks x, x + 8, x + 16 ... to XCD x: that
+// one takes a contiguous range (where nb, and the first block of the part, are multiples of 8).
+__host__ __device__ inline void place_of(const StepArgs& a, int L, int nb, int& chunk, int& tile) {
+  if ((nb & 7) == 0) L = (L & 7) * (nb >> 3) + (L >> 3);
+  const int ntiles = a.tiles_x * a.tiles_y;
+  chunk = L / ntiles;
+  tile = L - chunk * ntiles;
+}
+
 // Whether a tile of a lattice with lateral walls takes the plain population loads: none of its
 // cells and ring cells lies on a wall.  One launch covers all tiles; the others, the frame,
 // branch to the loads that mirror at the walls.  (One launch per part of the frame, each with

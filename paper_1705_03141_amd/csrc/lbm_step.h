@@ -311,7 +311,7 @@ struct PlaneState {
 #define LBM_STEP_WAVES_PER_EU 2
 #endif
 template <typename T, int TX, int TY, bool INIT, bool WALLS, bool BATCH>
-__device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb) {
+__device__ __forceinline__ void step_body(const StepArgs& A, const int L, const int nb) {
   using Tile = StepTile<TX, TY>;
   constexpr int NT = Tile::kThreads, NR = Tile::kRing, SX = Tile::SX, NS = Tile::kStaged, DX = Tile::DX,
                 ND = Tile::kDense, KS = Tile::kStagePerThread;
@@ -361,11 +361,8 @@ __device__ __forceinline__ void step_body(const StepArgs& A, int L, const int nb
   const unsigned slab_bytes = (unsigned)(Q * pb);           // 27 population planes of one z
   const unsigned sc_bytes = (unsigned)(5 * plane * 4);      // 5 scalar planes of one z
 
-  // block L of nb -> (z chunk, tile); XCD x receives blocks x, x + 8, ...: give it a
-  // contiguous range (nb and the first block of the range are multiples of 8 when remapped)
-  if ((nb & 7) == 0) L = (L & 7) * (nb >> 3) + (L >> 3);
-  const int ntiles = A.tiles_x * A.tiles_y;
-  const int chunk = L / ntiles, tile = L - chunk * ntiles;
+  int chunk, tile;
+  place_of(A, L, nb, chunk, tile);
   if (chunk >= A.nchunks) return;  // padding block of a batch (the whole block leaves)
   // a lattice of a batch that went unstable is not stepped further (the flag is read once per
   // workgroup, before any barrier; the whole workgroup leaves)
@@ -756,7 +753,7 @@ __global__ void __launch_bounds__(256)
 // ================================================================== launchers
 template <typename T, int TX, int TY, bool WALLS>
 hipError_t launch_step_walls(const StepArgs& a, hipStream_t s) {
-  const unsigned blocks = (unsigned)((long long)a.tiles_x * a.tiles_y * a.nchunks);
+  const unsigned blocks = (unsigned)step_blocks(a);
   if (a.init_mode)
     hipLaunchKernelGGL((step_kernel<T, TX, TY, true, WALLS>), dim3(blocks), dim3(TX * TY), 0, s, a);
   else
