@@ -858,7 +858,7 @@ static lbm_status build_groups(lbm_batch* b) {
         h[par].push_back(s);
       }
       const StepArgs& s = h[0].back();
-      first[j + 1] = first[j] + (int)((step_blocks(s) + 7) / 8 * 8);
+      first[j + 1] = first[j] + (int)step_blocks(s);
     }
     g.nblocks = first[n];
     bool ok = true;
@@ -1144,28 +1144,27 @@ extern "C" lbm_status lbm_selftest_tile_sets_host(const lbm_params* params, int 
   tmp.ty = ty;
   const bool walls = tmp.geo.wall_x || tmp.geo.wall_y;
   StepArgs s{};
-  // the step's map from blocks to places, walked over the whole grid of a launch and of a batch's part
-  // (padded to a multiple of 8), with a chunk per plane, some and one; a count other than 1 is kept
+  // the step's map from blocks to places, walked over the whole grid with a chunk per plane, some and
+  // one; a count other than 1 is kept
   std::vector<int> times, at;
-  for (const int zchunk : {1, 7, tmp.geo.nz})
-    for (const int pad : {1, 8}) {
-      tmp.zchunk = zchunk;
-      fill_step_args(&tmp, 0, 0, s);
-      const int tiles = s.tiles_x * s.tiles_y;
-      times.resize(tiles, 1);
-      const long long nb = (step_blocks(s) + pad - 1) / pad * pad;
-      if (zchunk < tmp.geo.nz && nb > (1ll << 24)) continue;
-      at.assign((size_t)tiles * s.nchunks, 0);
-      for (int L = 0; L < (int)nb; ++L) {
-        int chunk, tile;
-        place_of(s, L, (int)nb, chunk, tile);
-        if (chunk >= s.nchunks) continue;
-        if (chunk < 0 || tile < 0 || tile >= tiles) return fail(nullptr, LBM_EDEVICE, "a block outside of the lattice");
-        ++at[(size_t)chunk * tiles + tile];
-      }
-      for (size_t k = 0; k < at.size(); ++k)
-        if (at[k] != 1) times[k % tiles] = at[k];
+  for (const int zchunk : {1, 7, tmp.geo.nz}) {
+    tmp.zchunk = zchunk;
+    fill_step_args(&tmp, 0, 0, s);
+    const int tiles = s.tiles_x * s.tiles_y;
+    times.resize(tiles, 1);
+    const long long nb = step_blocks(s);
+    if (zchunk < tmp.geo.nz && nb > (1ll << 24)) continue;
+    at.assign((size_t)tiles * s.nchunks, 0);
+    for (int L = 0; L < (int)nb; ++L) {
+      int chunk, tile;
+      place_of(s, L, (int)nb, chunk, tile);
+      if (chunk >= s.nchunks) continue;
+      if (chunk < 0 || tile < 0 || tile >= tiles) return fail(nullptr, LBM_EDEVICE, "a block outside of the lattice");
+      ++at[(size_t)chunk * tiles + tile];
     }
+    for (size_t k = 0; k < at.size(); ++k)
+      if (at[k] != 1) times[k % tiles] = at[k];
+  }
   const int nt = s.tiles_x * s.tiles_y;
   for (int k = 0; k < 3 * nt; ++k) counts[k] = 0;
   for (int t = 0; t < nt; ++t) {

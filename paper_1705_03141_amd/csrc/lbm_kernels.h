@@ -42,14 +42,16 @@ struct StepArgs {
   GroupRates rates;
 };
 
-// Blocks of a step's launch.
-inline long long step_blocks(const StepArgs& a) { return (long long)a.tiles_x * a.tiles_y * a.nchunks; }
+// Blocks of a lattice's launch, or of its part of a batch's: a multiple of 8.
+inline long long step_blocks(const StepArgs& a) { return ((long long)a.tiles_x * a.tiles_y * a.nchunks + 7) / 8 * 8; }
 
-// Block L of the nb blocks of a lattice (its launch, or its part of a batch's) -> z chunk and tile; a chunk
-// from nchunks on is a block of padding.  The hardware sends blocks x, x + 8, x + 16 ... to XCD x: that
-// one takes a contiguous range (where nb, and the first block of the part, are multiples of 8).
+// Block L of the nb blocks of a lattice -> z chunk and tile; a chunk from nchunks on is a block of
+// padding.  The hardware sends blocks x, x + 8, x + 16 ... to XCD x: that one takes a contiguous range,
+// so that neighbouring tiles share an L2.  (With the blocks as they come, where their number is no
+// multiple of 8: 85^3 80 against 57 us per step in FP32, 70^3 57 against 43, 150^3 323 against 269,
+// 60^3 31.6 against 29.3.)
 __host__ __device__ inline void place_of(const StepArgs& a, int L, int nb, int& chunk, int& tile) {
-  if ((nb & 7) == 0) L = (L & 7) * (nb >> 3) + (L >> 3);
+  L = (L & 7) * (nb >> 3) + (L >> 3);
   const int ntiles = a.tiles_x * a.tiles_y;
   chunk = L / ntiles;
   tile = L - chunk * ntiles;
