@@ -359,17 +359,28 @@ static int auto_zchunk(const lbm_ctx* c, int tx, int ty, long long* cost = nullp
   return walls && c->p.storage == LBM_F32 && short_cost >= 0 && 20 * short_cost <= 21 * best_cost ? shorter : best;
 }
 
-// Tile shape when none is set: of 64 x 4 and 32 x 8 the one with the smaller cost (rounds x
-// planes), 64 x 4 where they are equal.  The wider rows are the faster shape for the same work
-// (the jet 256x256x1024: 4.01 against 4.42 ms), but narrow or ragged lattices pad less with the
-// other: 96^3 68 against 83 us, 85^3 79 against 83, 200x200x500 between walls 1.88 against
-// 1.92 ms.
+// Whether 32 x 8 tiles are taken, from the work of a lattice in 64 x 4 and in 32 x 8 tiles.  For the same
+// work the wider rows are the faster shape, by up to 10 % (180^3 460 against 500 us in FP32, 413 against
+// 443 in FP16), so that the other must save a twelfth of it: narrow or ragged lattices pad less with it
+// (saving 25 %, 96^3 64 against 80 us; 20 %, 150^3 270 against 304; 9 %, 210^3 777 against 784 in FP32, 665
+// against 692 in FP16; 7 %, 200x200x500 1666 against 1605; 6 %, 330x100x100 311 against 274).  Between lateral
+// walls a twentieth is enough (6 %, 200x200x400 1461 against 1524, FP16 1263 against 1301).  At equal
+// work rows of less than 64 cells are the same either way to 1 % in FP16 and favour 64 x 4 by up to 3 %
+// in FP32; in BF16 they favour 32 x 8 (60^3 28.4 against 29.3 us, 40x40x200 40.9 against 42.3).
+static bool tall_tiles(const lbm_ctx* c, long long wide, long long tall) {
+  const Geo& G = c->geo;
+  if (wide == tall) return G.nx < 64 && c->p.storage == LBM_BF16;
+  return G.wall_x || G.wall_y ? 20 * tall < 19 * wide : 12 * tall < 11 * wide;
+}
+
+// Tile shape when none is set, by rounds x planes.
 static void auto_shape(const lbm_ctx* c, int& tx, int& ty) {
   long long wide = 0, tall = 0;
   (void)auto_zchunk(c, 64, 4, &wide);
   (void)auto_zchunk(c, 32, 8, &tall);
-  tx = tall < wide ? 32 : 64;
-  ty = tall < wide ? 8 : 4;
+  const bool t = tall_tiles(c, wide, tall);
+  tx = t ? 32 : 64;
+  ty = t ? 8 : 4;
 }
 
 // Lattices of at most this many cells for which no tile shape has been set are stepped by bricks
@@ -810,16 +821,36 @@ static void batch_tiling(lbm_batch* b) {
   long long columns = 0, resident = 0;
   int dev = 0;
   (void)hipGetDevice(&dev);
-  for (lbm_ctx* c : b->c) {
-    if (c->tx == 0) {
-      // the batch fills the device whatever the shape: the one with fewer columns, which have
-      // fewer idle lanes (96 cells wide: 36 of 32 x 8 against 48 of 64 x 4)
+  // Shapes not set.  Rows of more than 64 cells go by the number of columns where the batch fills the
+  // device whatever the shape (96 cells wide: 36 of 32 x 8 against 48 of 64 x 4), else by what the lattice
+  // would take with chunks of its own (160x160x320 and 200x200x400 in FP32 1776 us, by columns 1880), if
+  // that differs.  Rows of at most 32 take 32 x 8, and those between join what there is in 32 x 8, so that
+  // small lattices share a launch (30x30x60, 40x40x80, 50x50x100 and 62x62x124: 124 us, in two launches
+  // 130); by themselves they take 64 x 4, and 32 x 8 in BF16 (five of 40 to 64 cells: FP32 258 against 277
+  // us, FP16 246 against 249, BF16 250 against 234).
+  long long most = 0;
+  for (const lbm_ctx* c : b->c) most += (long long)((c->geo.nx + 63) / 64) * ((c->geo.ny + 3) / 4);
+  bool any_tall = false;
+  for (const bool last : {false, true})
+    for (lbm_ctx* c : b->c) {
+      if (c->tx != 0) continue;
       const Geo& G = c->geo;
-      const long long wide = (long long)((G.nx + 63) / 64) * ((G.ny + 3) / 4);
-      const long long tall = (long long)((G.nx + 31) / 32) * ((G.ny + 7) / 8);
-      c->tx = tall < wide ? 32 : 64;
-      c->ty = tall < wide ? 8 : 4;
+      long long wide = (long long)((G.nx + 63) / 64) * ((G.ny + 3) / 4);
+      long long tall = (long long)((G.nx + 31) / 32) * ((G.ny + 7) / 8);
+      if (G.nx > 64 && most < step_resident_blocks((int)c->p.storage, 64, 4, dev)) {
+        long long w = 0, t = 0;
+        (void)auto_zchunk(c, 64, 4, &w);
+        (void)auto_zchunk(c, 32, 8, &t);
+        if (w != t) wide = w, tall = t;
+      }
+      const bool between = G.nx > 32 && G.nx <= 64;
+      if (between != last) continue;
+      const bool t = G.nx <= 32 || (between ? any_tall || c->p.storage == LBM_BF16 : tall_tiles(c, wide, tall));
+      any_tall |= t;
+      c->tx = t ? 32 : 64;
+      c->ty = t ? 8 : 4;
     }
+  for (const lbm_ctx* c : b->c) {
     columns += (long long)((c->geo.nx + c->tx - 1) / c->tx) * ((c->geo.ny + c->ty - 1) / c->ty);
     resident = std::max<long long>(resident, step_resident_blocks((int)c->p.storage, c->tx, c->ty, dev));
   }
