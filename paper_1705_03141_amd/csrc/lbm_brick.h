@@ -5,7 +5,7 @@
 // so a lattice too small to fill the device with long columns spends most of a step in that
 // serial prologue: three dependent pulls of 6 us each for columns of one plane.  Here every cell
 // the brick needs is pulled at once, each by its own thread, and the brick is collided after one
-// barrier: 2.3 to 2.8 pulls per cell instead of 1.5 (1 + 2 / planes), but one latency instead of
+// barrier: 2.5 or 2.8 pulls per cell instead of 1.5 (1 + 2 / planes), but one latency instead of
 // several, and no padding of rows to 32 or 64 cells.  Results are bitwise those of the
 // marching kernel: both complete a pull with finish_pull and collide with collide_cell.
 //
@@ -239,14 +239,9 @@ hipError_t launch_brick(const StepArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 8 x 4 x 4 cells while that gives every one of the 256 compute units at most one workgroup
-// (32^3: 9.8 us against 11.0 with the larger brick), else 16 x 4 x 4, which pulls 2.5 cells per
-// cell instead of 2.8 (48^3: 19.4 against 22.3 us).
 template <typename T>
 hipError_t launch_bricks_T(const StepArgs& a, hipStream_t s) {
-  const Geo& g = a.geo;
-  const long long small = (long long)((g.nx + 7) / 8) * ((g.ny + 3) / 4) * ((g.nz + 3) / 4);
-  return small <= 256 ? launch_brick<T, Brick<8, 4, 4>>(a, s) : launch_brick<T, Brick<16, 4, 4>>(a, s);
+  return small_bricks(a.geo) ? launch_brick<T, Brick<8, 4, 4>>(a, s) : launch_brick<T, Brick<16, 4, 4>>(a, s);
 }
 
 #define LBM_INSTANTIATE_BRICK(T) template hipError_t launch_bricks_T<T>(const StepArgs&, hipStream_t);

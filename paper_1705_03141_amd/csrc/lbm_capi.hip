@@ -373,24 +373,31 @@ static bool tall_tiles(const lbm_ctx* c, long long wide, long long tall) {
   return G.wall_x || G.wall_y ? 20 * tall < 19 * wide : 12 * tall < 11 * wide;
 }
 
-// Tile shape when none is set, by rounds x planes.
-static void auto_shape(const lbm_ctx* c, int& tx, int& ty) {
+// Tile shape when none is set, by rounds x planes; returns the work of the chosen one.
+static long long auto_shape(const lbm_ctx* c, int& tx, int& ty) {
   long long wide = 0, tall = 0;
   (void)auto_zchunk(c, 64, 4, &wide);
   (void)auto_zchunk(c, 32, 8, &tall);
   const bool t = tall_tiles(c, wide, tall);
   tx = t ? 32 : 64;
   ty = t ? 8 : 4;
+  return t ? tall : wide;
 }
 
-// Lattices of at most this many cells for which no tile shape has been set are stepped by bricks
-// (lbm_brick.h): faster up to 48^3 at least, slower from 64^3.
+// Lattices of at most kBrickCells cells for which no tile shape has been set are stepped by bricks
+// (lbm_brick.h) if their rounds of workgroups take no longer than the planes that a column goes
+// through: a round takes 8 to 10 us, a plane about 7.  FP32, bricks against columns: 48^3 two rounds, four
+// planes, 19 against 28 us; 40^3 two, three, 21 against 22; 36x36x100 three, four, 28.0 against 28.7
+// (BF16 25.6 against 29.2; but 50^3 32.7 against 28.2); 8x8x2048 four, six, 33 against 41.  Flat lattices
+// leave bricks half empty: 256x256x2 four, three, 31 against 23; 360x360x1 nine, six, 61 against 38;
+// 150x150x5 three, three, 28 against 23.  Larger lattices always have more rounds than planes (64^3 40
+// against 30).
 static constexpr long long kBrickCells = 1ll << 17;
 
 static void choose_tiling(lbm_ctx* c) {
   if (c->tx == 0) {
-    c->bricks = c->geo.n <= kBrickCells;
-    auto_shape(c, c->tx, c->ty);
+    const long long planes = auto_shape(c, c->tx, c->ty);
+    c->bricks = c->geo.n <= kBrickCells && 4 * brick_rounds(c->geo) <= 3 * planes;
   }
   if (c->zchunk < 1) c->zchunk = auto_zchunk(c, c->tx, c->ty);
 }
