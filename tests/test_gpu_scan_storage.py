@@ -1,0 +1,62 @@
+"""GPU test of the block means on the device and the diagnostics for every storage type, against the
+per-cell read-back of the same lattice, which isolates them from the error of 16-bit storage: an
+inflow disk and an outlet plane, lateral walls, body force, ragged rows, and lattices so narrow that
+a cell per thread is the faster form (factor 1 and the diagnostics)."""
+import numpy as np
+import pytest
+
+from paper_1705_03141_amd import lbm
+from paper_1705_03141_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _drop(*dims):
+    return W.static_droplet(dims=dims, radius=0.3 * min(dims) + 0.5, rho_r0=1.5, rho_b0=1.0, nu=0.05, A=0.01)
+
+
+PROBLEMS = {
+    "ragged": lambda: _drop(68, 20, 24), "columns of one tile": lambda: _drop(64, 4, 40),
+    "jet": lambda: W.jet(nx=24, ny=24, nz=48, diameter=8.0),
+    "jet between walls": lambda: W.jet(nx=72, ny=20, nz=40, diameter=8.0, eta=4.2, lateral=W.FREESLIP),
+    "rt": lambda: W.rayleigh_taylor(width=16, height=48, g=1e-4, reynolds=64.0),
+    "10 wide": lambda: _drop(10, 40, 12), "11 wide": lambda: _drop(11, 40, 12), "8 wide": lambda: _drop(8, 16, 64),
+    "one cell wide": lambda: _drop(1, 30, 36), "one row": lambda: _drop(65, 1, 30),
+    "narrow jet": lambda: W.jet(nx=8, ny=12, nz=37, diameter=6.0),
+    "narrow jet between walls": lambda: W.jet(nx=8, ny=8, nz=32, diameter=6.0, eta=4.2, lateral=W.FREESLIP),
+}
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("name", list(PROBLEMS))
+def test_against_read_back(name, storage):
+    import torch
+    pb = PROBLEMS[name]()
+    lat = lbm.Lattice(pb, storage=storage)
+    u_scale = 0.02
+    for steps in (0, 6):
+        lat.step(steps)
+        f = lat.fields()
+        nz, ny, nx = f["phi"].shape
+        for k in (1, 2, 4):
+            if nx % k or ny % k or nz % k:
+                continue
+            box = torch.full((nz // k + 1, ny // k + 2, nx // k + 3, 4), 7.0, device="cuda")
+            lat.coarse_state_into(box, k, u_scale)
+            got = box.cpu().numpy()
+            for c, v in enumerate([f["phi"]] + [f["u"][d] / u_scale for d in range(3)]):
+                want = v.reshape(nz // k, k, ny // k, k, nx // k, k).mean(axis=(1, 3, 5))
+                # FP32: a velocity's 27 terms of magnitude 0.05 over u_scale, and a sum of 64 values up to 3
+                assert np.abs(got[:nz // k, :ny // k, :nx // k, c] - want).max() < 2e-5, (steps, k, c)
+            assert (got[nz // k:] == 7.0).all() and (got[:, ny // k:] == 7.0).all() and (got[:, :, nx // k:] == 7.0).all()
+        cen, r_in, r_out = ((nx - 1) / 2, (ny - 1) / 2, (nz - 1) / 2), 3.0, 6.0
+        d = lat.diagnostics(center=cen, r_in=r_in, r_out=r_out)
+        z, y, x = np.meshgrid(np.arange(nz), np.arange(ny), np.arange(nx), indexing="ij")
+        r = np.sqrt((x - cen[0]) ** 2 + (y - cen[1]) ** 2 + (z - cen[2]) ** 2)
+        total = f["rho"].sum()
+        assert d["n_in"] == (r <= r_in).sum() and d["n_out"] == (r >= r_out).sum() and d["nan_cells"] == 0
+        # (the outlet plane, formed otherwise, may differ by an ulp of FP32 per cell)
+        assert abs(d["mass_r"] - f["rho_r"].sum()) < 2e-7 * total and abs(d["mass_b"] - f["rho_b"].sum()) < 2e-7 * total
+        assert abs(d["p_in"] - f["p"][r <= r_in].mean()) < 1e-6 and abs(d["p_out"] - f["p"][r >= r_out].mean()) < 1e-6
+        assert abs(d["umax"] - np.sqrt((f["u"] ** 2).sum(0)).max()) < 1e-6
+    lat.close()
