@@ -218,8 +218,7 @@ extern "C" lbm_status lbm_create(const lbm_params* params, void* hip_stream, lbm
     if (c->geo.face_hi == FACE_OUTFLOW)
       ok &= hipMalloc((void**)&c->outlet[k], plane * kOutletPlanes * sizeof(float)) == hipSuccess;
   }
-  ok = ok && hipMalloc((void**)&c->diag_part, (size_t)scan_blocks(scan_plan(c->geo, 1)) * 8 * sizeof(double)) ==
-                 hipSuccess;
+  ok = ok && hipMalloc((void**)&c->diag_part, (size_t)diag_blocks(c->geo) * 8 * sizeof(double)) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->diag_out, 8 * sizeof(double)) == hipSuccess;
   ok = ok && hipMalloc((void**)&c->unstable, sizeof(int)) == hipSuccess &&
        hipMemset(c->unstable, 0, sizeof(int)) == hipSuccess;

@@ -112,22 +112,37 @@ struct ScanArgs {
 
 inline long long scan_blocks(const ScanArgs& r) { return (long long)r.tiles_x * r.tiles_y * r.nchunks; }
 
+// Whether a lattice uses less than a sixth of the lanes of its 64 x 4 columns: a cell per thread is
+// faster then, although it loads the scalars of all 26 neighbours (coarse state with factor 1 and
+// diagnostics, us: 8x40x300 21 and 63 against 23 and 73, 1x360x360 19 and 63 against 189 and 259;
+// 12x200x400 the other way, 141 and 172 against 114 and 162).
+inline bool scan_idle(const Geo& g) {
+  return 6ll * g.nx * g.ny < 256ll * ((g.nx + 63) / 64) * ((g.ny + 3) / 4);
+}
+
 // The longest chunk, up to 32 planes, that still gives every place for a workgroup (4 on each of
 // 256 compute units) one; a multiple of the factor; and not so that the last chunk is the
-// outlet plane alone, whose state is formed from the plane below.
-inline ScanArgs scan_plan(const Geo& g, int factor) {
+// outlet plane alone, whose state is formed from the plane below.  The diagnostics, whose blocks each
+// leave a partial sum that one workgroup adds up, make do with 400 blocks below 8 planes (a
+// call on 64x1x2000 63 us with 500 blocks of 4 planes, 69 with 2000 of one; 85^3 73 with 968, 79 with 1892).
+inline ScanArgs scan_plan(const Geo& g, int factor, ScanKind kind) {
   ScanArgs r{};
   r.tiles_x = (g.nx + 63) / 64;
   r.tiles_y = (g.ny + 3) / 4;
   const long long tiles = (long long)r.tiles_x * r.tiles_y;
   int zc = 32;
-  while (zc > factor && tiles * ((g.nz + zc - 1) / zc) < 1024) zc /= 2;
+  while (zc > factor && tiles * ((g.nz + zc - 1) / zc) < (kind == kScanDiag && zc < 8 ? 400 : 1024)) zc /= 2;
   if (zc > g.nz) zc = g.nz;
   if (g.face_hi == FACE_OUTFLOW)
     while (zc == 1 || g.nz % zc == 1) ++zc;
   r.zchunk = zc;
   r.nchunks = (g.nz + zc - 1) / zc;
   return r;
+}
+
+// Blocks of the diagnostics, each of which leaves 8 doubles.
+inline long long diag_blocks(const Geo& g) {
+  return scan_idle(g) ? (g.n + 255) / 256 : scan_blocks(scan_plan(g, 1, kScanDiag));
 }
 
 // Typed launchers, instantiated once per storage type (lbm_storage_*.hip).

@@ -475,7 +475,8 @@ __global__ void __launch_bounds__(256) fields_kernel(const AuxArgs A, int x0, in
 
 // Coarse-grained state: (phi, ux/u_scale, uy/u_scale, uz/u_scale) averaged over f^3 blocks of
 // cells, written as FP32 into out[cz][cy][cx][4] of a padded box of pd x ph x pw voxels, one thread
-// a block.  For factors that the tile of scan_kernel does not hold (1, 2 and 4 take that one).
+// a block.  For factors that the tile of scan_kernel does not hold (1, 2 and 4 take that one), and factor 1
+// where a lattice leaves most of the tile's lanes idle.
 template <typename T>
 __global__ void __launch_bounds__(256) coarse_kernel(const AuxArgs A, int f, float inv_u, float* __restrict__ out,
                                                      int ph, int pw) {
@@ -520,7 +521,64 @@ __global__ void __launch_bounds__(256) populations_kernel(const AuxArgs A, doubl
   }
 }
 
-// Diagnostics: the per-block FP64 partial sums of scan_kernel together, in a fixed order.
+// Diagnostics of lattices that leave most lanes of scan_kernel's tiles idle, a cell per thread:
+// per-block FP64 partial sums, reduced in a fixed order by diag_finish_kernel.
+//   part[b] = {mass_r, mass_b, p_in, n_in, p_out, n_out, bad cells, umax}
+template <typename T>
+__global__ void __launch_bounds__(256) diag_kernel(const AuxArgs A, DiagQuery Qy, double* __restrict__ part) {
+  const Geo& G = A.geo;
+  const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  double v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  if (c < G.n) {
+    const int x = (int)(c % G.nx), y = (int)((c / G.nx) % G.ny), z = (int)(c / G.plane);
+    float rho, rho_r, rho_b, j[3], fr[Q], fb[Q];
+    cell_state<T>(A, x, y, z, rho, rho_r, rho_b, j, fr, fb, false);
+    const double rr = rho_r, rb = rho_b;
+    float F[3];
+    body_force(A, rho, F);
+    if (is_inflow(G, x, y, z)) F[0] = F[1] = F[2] = 0.0f;
+    const double ux = ((double)j[0] + 0.5 * F[0]) / rho, uy = ((double)j[1] + 0.5 * F[1]) / rho,
+                 uz = ((double)j[2] + 0.5 * F[2]) / rho;
+    const double p = rr * 9.0 * (1.0 - (double)A.pc.alpha_r) / 19.0 + rb * 9.0 * (1.0 - (double)A.pc.alpha_b) / 19.0;
+    const double dx = x - Qy.xc, dy = y - Qy.yc, dz = z - Qy.zc;
+    const double r = sqrt(dx * dx + dy * dy + dz * dz);
+    const bool bad = !(rho > 0.0f) || isnan(rho_r) || isnan(rho_b) || isnan(j[0]) || isnan(j[1]) || isnan(j[2]);
+    v[0] = rr;
+    v[1] = rb;
+    if (r <= Qy.r_in) {
+      v[2] = p;
+      v[3] = 1.0;
+    }
+    if (r >= Qy.r_out) {
+      v[4] = p;
+      v[5] = 1.0;
+    }
+    v[6] = bad ? 1.0 : 0.0;
+    v[7] = bad ? 0.0 : sqrt(ux * ux + uy * uy + uz * uz);
+  }
+  // wave64 butterfly reduction, then across the 4 waves through LDS
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+      const double o = __shfl_xor(v[k], off, 64);
+      v[k] = (k == 7) ? fmax(v[k], o) : v[k] + o;
+    }
+  }
+  __shared__ double red[4][8];
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+  if (lane == 0)
+    for (int k = 0; k < 8; ++k) red[wave][k] = v[k];
+  __syncthreads();
+  if (threadIdx.x < 8) {
+    const int k = threadIdx.x;
+    double s = red[0][k];
+    for (int w = 1; w < 4; ++w) s = (k == 7) ? fmax(s, red[w][k]) : s + red[w][k];
+    part[(long long)blockIdx.x * 8 + k] = s;
+  }
+}
+
+// The partial sums of scan_kernel or diag_kernel together, in a fixed order.
 static __global__ void __launch_bounds__(256) diag_finish_kernel(const double* __restrict__ part, long long nblocks,
                                                           double* __restrict__ out) {
   // fixed-order reduction: thread t sums blocks t, t+256, ...; then a tree over threads

@@ -293,8 +293,8 @@ hipError_t launch_scan(const AuxArgs& a, const ScanArgs& r, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_coarse_T(const AuxArgs& a, int f, float inv_u, float* out, int ph, int pw, hipStream_t s) {
-  if (f == 1 || f == 2 || f == 4) {  // the factors that divide the tile
-    ScanArgs r = scan_plan(a.geo, f);
+  if ((f == 1 && !scan_idle(a.geo)) || f == 2 || f == 4) {  // the factors that divide the tile
+    ScanArgs r = scan_plan(a.geo, f, kScanCoarse);
     r.factor = f;
     r.inv_u = inv_u;
     r.out = out;
@@ -307,15 +307,21 @@ hipError_t launch_coarse_T(const AuxArgs& a, int f, float inv_u, float* out, int
   return hipGetLastError();
 }
 
-// part: 8 doubles for each of the scan_blocks(scan_plan(geo, 1)) blocks
+// part: 8 doubles for each of the diag_blocks(geo) blocks
 template <typename T>
 hipError_t launch_diag_T(const AuxArgs& a, const DiagQuery& q, double* part, double* out, hipStream_t s) {
-  ScanArgs r = scan_plan(a.geo, 1);
-  r.q = q;
-  r.part = part;
-  const hipError_t e = launch_scan<T, kScanDiag>(a, r, s);
+  hipError_t e;
+  if (scan_idle(a.geo)) {
+    hipLaunchKernelGGL(diag_kernel<T>, dim3((unsigned)diag_blocks(a.geo)), dim3(256), 0, s, a, q, part);
+    e = hipGetLastError();
+  } else {
+    ScanArgs r = scan_plan(a.geo, 1, kScanDiag);
+    r.q = q;
+    r.part = part;
+    e = launch_scan<T, kScanDiag>(a, r, s);
+  }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(256), 0, s, part, scan_blocks(r), out);
+  hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(256), 0, s, part, diag_blocks(a.geo), out);
   return hipGetLastError();
 }
 
