@@ -5,10 +5,11 @@
 // Convolution.  out[v][co] = sum_tap sum_ci in[v + off(tap)][ci] w[tap][co][ci] is a GEMM with
 // M = voxels, N = cout, K = 27 cin.  The kernels that carry the network (conv_slide_kernel;
 // conv_box_kernel for the 8-channel input; wgrad_kernel) stage their operands through LDS and
-// issue v_mfma_f32_32x32x16_bf16; conv_staged_kernel takes small volumes of 64 channels, and
+// issue v_mfma_f32_32x32x16_bf16; conv_staged_kernel takes small volumes of 64 channels, and planes
+// of 2^31 and more elements with 32 or 64, too large for the sliding kernel's 32-bit offsets;
 // conv_fwd_kernel, the direct form with one wave per 32 voxels x 32 output channels and
-// v_mfma_f32_32x32x8_bf16 fed from global memory, channel counts the others do not take (cin = 128,
-// and planes too large for 32-bit offsets).
+// v_mfma_f32_32x32x8_bf16 fed from global memory, takes 128 channels.  Tensors and weights may have any
+// alignment that their values have.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -19,6 +20,7 @@
 namespace {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x4_any __attribute__((ext_vector_type(4), aligned(2), may_alias));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
@@ -27,6 +29,18 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
                                                  0);
+}
+
+// 16 bytes of global memory at any address a BF16 (or FP32) value may have: one instruction all the
+// same, the hardware takes wide accesses at every alignment.
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2), may_alias));
+__device__ __forceinline__ uint4 load16(const uint16_t* p) {
+  const u32x4_any v = *reinterpret_cast<const u32x4_any*>(p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <typename T>
+__device__ __forceinline__ void store16(T* p, uint4 v) {
+  *reinterpret_cast<u32x4_any*>(p) = u32x4_any{v.x, v.y, v.z, v.w};
 }
 
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
@@ -114,13 +128,13 @@ __global__ void __launch_bounds__(256) conv_fwd_kernel(const uint16_t* __restric
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
       a[k] = bf16x4{0, 0, 0, 0};
-      if (inb) a[k] = *reinterpret_cast<const bf16x4*>(arow + 8 * k);
+      if (inb) a[k] = *reinterpret_cast<const bf16x4_any*>(arow + 8 * k);
     }
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
       const uint16_t* brow = w + ((long long)tap * cout + co0 + 32 * j + (lane & 31)) * CIN + kq;
 #pragma unroll
-      for (int k = 0; k < KS; ++k) b[j][k] = *reinterpret_cast<const bf16x4*>(brow + 8 * k);
+      for (int k = 0; k < KS; ++k) b[j][k] = *reinterpret_cast<const bf16x4_any*>(brow + 8 * k);
     }
 #pragma unroll
     for (int k = 0; k < KS; ++k)
@@ -158,7 +172,7 @@ void launch_conv(const uint16_t* in, const uint16_t* w, const float* bias, uint1
 }
 
 // ---------------------------------------------------------------- forward convolution, staged
-// For cin in {16, 32, 64}: a block of NW waves owns a co tile of 32 and walks tiles of two
+// For cin in {32, 64}: a block of NW waves owns a co tile of 32 and walks tiles of two
 // output rows x SEG voxels (grid-stride).  Per tile it stages into LDS every input voxel the
 // tile reads -- 3 z-planes x 4 rows x (SEG + 2) voxels, all cin channels, zeros outside the
 // volume -- with a voxel stride of cin + 8 elements (4 x an odd number of dwords, so each
@@ -207,7 +221,7 @@ __global__ void __launch_bounds__(64 * StagedConv<CIN>::NW, 2) conv_staged_kerne
     wb[i] = make_uint4(0, 0, 0, 0);
     if (i < nk) {
       const int k = k0 + i, tap = k / P::SL, sl = k % P::SL;
-      wb[i] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + c) * CIN + sl * 16 + 8 * h);
+      wb[i] = load16(w + ((long long)tap * cout + co0 + c) * CIN + sl * 16 + 8 * h);
     }
   }
   const float bb = bias ? bias[co0 + c] : 0.0f;
@@ -229,7 +243,7 @@ __global__ void __launch_bounds__(64 * StagedConv<CIN>::NW, 2) conv_staged_kerne
       const int dz = row / 4 - 1, ys = y0 + row % 4 - 1, zs = z + dz, x = x0 + v - 1;
       uint4 val = make_uint4(0, 0, 0, 0);
       if (zs >= 0 && zs < D && ys >= 0 && ys < H && x >= 0 && x < W)
-        val = *reinterpret_cast<const uint4*>(in + (((nz + dz) * H + ys) * (long long)W + x) * CIN + 8 * q);
+        val = load16(in + (((nz + dz) * H + ys) * (long long)W + x) * CIN + 8 * q);
       *reinterpret_cast<uint4*>(st + (row * P::RV + v) * P::VS + 8 * q) = val;
     }
     __syncthreads();
@@ -299,228 +313,6 @@ __global__ void __launch_bounds__(64 * StagedConv<CIN>::NW, 2) conv_staged_kerne
   }
 }
 
-// ---------------------------------------------------------------- forward convolution, z ring
-// For cin in {8, 16, 32}, where a buffer is not aligned to 16 bytes: as the staged kernel (four waves split the K-steps, weights in
-// registers, output tiles of two rows x 64 voxels), but a block owns a column (n, row pair,
-// segment) and sweeps a range of z: the three input planes z - 1, z, z + 1 (4 rows x 66
-// voxels each) live in a ring in LDS, so each output plane stages one new plane, and the
-// loads of plane z + 2 are issued before the MFMAs of plane z and stored after them.  The
-// four partial sums of the four M-tiles are exchanged in three rounds through a separate
-// buffer: in round r wave w passes its partial of tile (w + r + 1) % 4 to the wave that owns
-// that tile, which adds it to its own (a fixed order per tile).  With 8 channels a K-step
-// pairs two taps: lane half h takes tap 2 k + h (k = 13: tap 26 and a zero weight), and the
-// voxel stride of 8 elements (4 dwords) is already conflict-free.
-template <int CIN>
-struct RingConv {
-  static constexpr int SEG = 64, XT = 2, MT = 4, NW = 4;
-  static constexpr int RV = SEG + 2;                 // staged voxels per row
-  static constexpr int VS = CIN == 8 ? 8 : CIN + 8;  // staged voxel stride (elements)
-  static constexpr int SL = CIN == 8 ? 1 : CIN / 16; // MFMA K-steps per tap (per tap pair for 8)
-  static constexpr int Q = CIN / 8;                  // 16-byte chunks of a voxel
-  static constexpr int KSTEPS = CIN == 8 ? 14 : 27 * SL, IPW = (KSTEPS + NW - 1) / NW;
-  static constexpr int PLANE = 4 * RV * VS;          // elements of a staged plane
-  static constexpr int CHUNKS = 4 * RV * Q;          // 16-byte chunks of a plane
-  static constexpr int PF = (CHUNKS + 64 * NW - 1) / (64 * NW);  // chunks per thread
-};
-
-template <int CIN>
-__global__ void __launch_bounds__(256, 2) conv_ring_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ w,
-                                                           const float* __restrict__ bias, uint16_t* __restrict__ out,
-                                                           float* __restrict__ out_f32, int D, int H, int W, int cout,
-                                                           int relu, int nzc, int zlen, long long nitems) {
-  using P = RingConv<CIN>;
-  __shared__ __align__(16) uint16_t ring[3 * P::PLANE];
-  __shared__ __align__(16) float xch[P::NW * 1024];
-  const int t = threadIdx.x, lane = t & 63, h = lane >> 5, c = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int co0 = blockIdx.y * 32;
-  const int k0 = P::KSTEPS * wave / P::NW, nk = P::KSTEPS * (wave + 1) / P::NW - k0;
-
-  uint4 wb[P::IPW];
-#pragma unroll
-  for (int i = 0; i < P::IPW; ++i) {
-    wb[i] = make_uint4(0, 0, 0, 0);
-    if (i < nk) {
-      const int k = k0 + i;
-      if constexpr (CIN == 8) {
-        const int tap = 2 * k + h;
-        if (tap < 27) wb[i] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + c) * CIN);
-      } else {
-        const int tap = k / P::SL, sl = k % P::SL;
-        wb[i] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + c) * CIN + sl * 16 + 8 * h);
-      }
-    }
-  }
-  const float bb = bias ? bias[co0 + c] : 0.0f;
-  const int lane_off = c * P::VS + (CIN == 8 ? 0 : 8 * h);
-  const int nseg = (W + P::SEG - 1) / P::SEG, nyp = (H + 1) / 2;
-  const long long plane_elems = (long long)H * W * CIN;
-  // wave w owns output tile w: row y0 + w / 2, voxels x0 + 32 (w % 2) ..
-  const int my_row = wave / P::XT, my_x = (wave % P::XT) * 32;
-
-  // the staged chunks this thread moves: offset within an input plane (-1 where the voxel
-  // is outside the plane or the chunk index is past the plane)
-  int src_off[P::PF];
-
-  auto store_plane = [&](int p, const uint4(&buf)[P::PF]) {
-    uint16_t* dst = ring + ((p + 3) % 3) * P::PLANE;
-#pragma unroll
-    for (int k = 0; k < P::PF; ++k) {
-      const int it = t + 64 * P::NW * k;
-      if (it < P::CHUNKS) {
-        const int q = it % P::Q, v = (it / P::Q) % P::RV, r = it / (P::Q * P::RV);
-        *reinterpret_cast<uint4*>(dst + (r * P::RV + v) * P::VS + 8 * q) = buf[k];
-      }
-    }
-  };
-
-#pragma unroll 1
-  for (long long item = blockIdx.x; item < nitems; item += gridDim.x) {
-    const int zc = (int)(item % nzc);
-    const long long col = item / nzc;  // (n nyp + yp) nseg + seg
-    const int seg = (int)(col % nseg);
-    const int yp = (int)((col / nseg) % nyp);
-    const long long nb = col / ((long long)nseg * nyp);
-    const int x0 = seg * P::SEG, y0 = 2 * yp;
-    const int za = zc * zlen, zb = min(D, za + zlen);
-    const uint16_t* in_n = in + nb * D * plane_elems;
-#pragma unroll
-    for (int k = 0; k < P::PF; ++k) {
-      const int it = t + 64 * P::NW * k;
-      src_off[k] = -1;
-      if (it < P::CHUNKS) {
-        const int q = it % P::Q, v = (it / P::Q) % P::RV, r = it / (P::Q * P::RV);
-        const int ys = y0 + r - 1, x = x0 + v - 1;
-        if (ys >= 0 && ys < H && x >= 0 && x < W) src_off[k] = (ys * W + x) * CIN + 8 * q;
-      }
-    }
-    auto load = [&](int p, uint4(&buf)[P::PF]) {
-      const bool pin = p >= 0 && p < D;
-      const uint16_t* base = in_n + (long long)p * plane_elems;
-#pragma unroll
-      for (int k = 0; k < P::PF; ++k) {
-        buf[k] = make_uint4(0, 0, 0, 0);
-        if (pin && src_off[k] >= 0) buf[k] = *reinterpret_cast<const uint4*>(base + src_off[k]);
-      }
-    };
-
-    uint4 pf[P::PF];
-    __syncthreads();  // the previous item's reads of the ring are done
-    load(za - 1, pf);
-    store_plane(za - 1, pf);
-    load(za, pf);
-    store_plane(za, pf);
-    load(za + 1, pf);
-    int sm = ((za + 2) % 3) * P::PLANE, s0 = (za % 3) * P::PLANE, sp = ((za + 1) % 3) * P::PLANE;  // z - 1, z, z + 1
-#pragma unroll 1
-    for (int z = za; z < zb; ++z) {
-      store_plane(z + 1, pf);  // its slot held plane z - 2, last read before the previous exchange
-      __syncthreads();
-      if (z + 1 < zb) load(z + 2, pf);
-
-      floatx16 acc[P::MT];
-#pragma unroll
-      for (int m = 0; m < P::MT; ++m) acc[m] = floatx16{};
-      int lo = lane_off;
-      asm volatile("" : "+v"(lo));  // keeps the per-step A addresses inside the z loop
-#pragma unroll
-      for (int i = 0; i < P::IPW; ++i) {
-        if (i < nk) {
-          const int k = k0 + i;
-          int tap, sl;
-          if constexpr (CIN == 8) {
-            tap = min(2 * k + h, 26);  // lane-dependent; the zero weight of tap 27 reads tap 26
-            sl = 0;
-          } else {
-            tap = k / P::SL;
-            sl = k % P::SL;
-          }
-          const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;  // each offset + 1
-          const int sb = dz == 0 ? sm : (dz == 1 ? s0 : sp);
-          const uint16_t* a0 = ring + sb + (dy * P::RV + dx) * P::VS + sl * 16 + lo;
-#pragma unroll
-          for (int m = 0; m < P::MT; ++m) {
-            const int moff = (m / P::XT) * P::RV * P::VS + (m % P::XT) * 32 * P::VS;
-            acc[m] = mfma16(*reinterpret_cast<const uint4*>(a0 + moff), wb[i], acc[m]);
-          }
-        }
-      }
-      {
-        const int tmp = sm;
-        sm = s0;
-        s0 = sp;
-        sp = tmp;
-      }
-
-      // the partial sums: round r, wave w sends tile (w + r + 1) % 4 and adds the one from
-      // wave (w - r - 1) % 4 to its own tile w (copies chosen by wave-uniform branches keep
-      // the accumulators in registers)
-      floatx16 mine = acc[0];
-      if (wave == 1) mine = acc[1];
-      if (wave == 2) mine = acc[2];
-      if (wave == 3) mine = acc[3];
-#pragma unroll
-      for (int r = 0; r < P::NW - 1; ++r) {
-        const int send = (wave + r + 1) % P::NW, from = (wave + P::NW - r - 1) % P::NW;
-        floatx16 snd = acc[0];
-        if (send == 1) snd = acc[1];
-        if (send == 2) snd = acc[2];
-        if (send == 3) snd = acc[3];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) xch[wave * 1024 + e * 64 + lane] = snd[e];
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 16; ++e) mine[e] += xch[from * 1024 + e * 64 + lane];
-        __syncthreads();
-      }
-      const int y = y0 + my_row;
-      if (y < H) {
-        // element e of the tile is voxel xb + (e / 4) * 8 + e % 4; one base per step and
-        // per-element offsets in multiples of cout (made opaque so they are not hoisted out
-        // of the z loop as 16 separate 64-bit addresses)
-        int co = cout;
-        asm volatile("" : "+s"(co));
-        const int xb = x0 + my_x + 4 * h;
-        const long long obase = (((nb * D + z) * H + y) * (long long)W + xb) * co + co0 + c;
-        if (out_f32) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            if (xb + (e / 4) * 8 + (e & 3) < W) {
-              const float val = mine[e] + bb;
-              out_f32[obase + ((e / 4) * 8 + (e & 3)) * co] = relu ? fmaxf(val, 0.0f) : val;
-            }
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            if (xb + (e / 4) * 8 + (e & 3) < W) {
-              const float val = mine[e] + bb;
-              out[obase + ((e / 4) * 8 + (e & 3)) * co] = f2bf(relu ? fmaxf(val, 0.0f) : val);
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-template <int CIN>
-void launch_ring(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32, int n, int d,
-                 int h, int wd, int cout, int relu, hipStream_t s) {
-  using P = RingConv<CIN>;
-  const int ctiles = cout / 32;
-  const long long ncols = (long long)n * ((h + 1) / 2) * ((wd + P::SEG - 1) / P::SEG);
-  const long long target = (512 + ctiles - 1) / ctiles;  // two resident blocks on each of 256 CUs
-  long long nzc = (target + ncols - 1) / ncols;
-  if (nzc > d) nzc = d;
-  const int zlen = (int)((d + nzc - 1) / nzc);
-  nzc = (d + zlen - 1) / zlen;
-  const long long nitems = ncols * nzc;
-  const unsigned gx = (unsigned)(nitems < target ? nitems : target);
-  hipLaunchKernelGGL(conv_ring_kernel<CIN>, dim3(gx, ctiles), dim3(256), 0, s, in, w, bias, out, out_f32, d, h, wd, cout,
-                     relu, (int)nzc, zlen, nitems);
-}
-
 template <int CIN>
 void launch_staged(const uint16_t* in, const uint16_t* w, const float* bias, uint16_t* out, float* out_f32, int n,
                    int d, int h, int wd, int cout, int relu, hipStream_t s) {
@@ -565,7 +357,8 @@ __device__ __forceinline__ void pack_halves(const floatx16& v, uint4 (&u)[2]) {
 __device__ __forceinline__ void store_f32x16(float* o, const floatx16& v, int h) {
 #pragma unroll
   for (int g = 0; g < 4; ++g)
-    *reinterpret_cast<float4*>(o + 8 * g + 4 * h) = make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]);
+    store16(o + 8 * g + 4 * h, make_uint4(__float_as_uint(v[4 * g]), __float_as_uint(v[4 * g + 1]),
+                                          __float_as_uint(v[4 * g + 2]), __float_as_uint(v[4 * g + 3])));
 }
 
 // ---------------------------------------------------------------- convolution, sliding
@@ -575,9 +368,10 @@ __device__ __forceinline__ void store_f32x16(float* o, const floatx16& v, int h)
 // row of 32 voxels) keeps the accumulators of three output planes (z - 1, z, z + 1) in registers,
 // and a fragment of voxels read from LDS feeds three MFMAs.  No partial sums pass between waves.
 //
-// The sums are in the order of the kernels that split the taps over the waves of a block (the ring
-// and staged kernels), so that results stay bitwise what they were: another order moves one BF16
-// activation in 10^4 by an ulp, which the network carries to 5e-4 of its prediction.  The K-steps
+// The sums are in the order of kernels that split the taps over the waves of a block, with 64 channels
+// that of conv_staged_kernel, so that small and large volumes agree bitwise and results stay what they
+// have been: another order moves one BF16 activation in 10^4 by an ulp, which the network carries to
+// 5e-4 of its prediction.  The K-steps
 // k = tap * SL + slice fall into NCHAIN chains of consecutive k, each summed from zero; with 64
 // channels the 8 chains are added in order, with 32 the 4 chains c as ((c_w + c_w-1) + c_w-2) +
 // c_w-3, indices modulo 4, w = 2 (y % 2) + x / 32 % 2; the bias comes last.  So the taps of a plane
@@ -594,8 +388,8 @@ __device__ __forceinline__ void store_f32x16(float* o, const floatx16& v, int h)
 // loads are issued before the MFMAs of the present one.
 //
 // What bounds it is the rate the card sustains on the matrix cores: an 8192^3 BF16 product reaches
-// 1180 TFLOP/s, a form of this kernel without its stores 1160.  Measured against the ring and
-// staged kernels (and their separate mask pass): 32 -> 32 on 1x256x64x64 97 -> 58 us (1000 TFLOP/s),
+// 1180 TFLOP/s, a form of this kernel without its stores 1160.  One layer repeated by itself, against
+// kernels that split the taps over the waves (and their separate mask pass): 32 -> 32 on 1x256x64x64 97 -> 58 us (1000 TFLOP/s),
 // FP32 result 95 -> 64, masked data gradient 123 -> 70; 1x128x32x32: 32 -> 64 49 -> 20 us, 64 -> 32
 // 63 -> 21; 64 -> 64 on 1x64x16x16 31 -> 15 us.  With 8-byte stores (no exchange between the halves)
 // the first three took 62, 65 and 81 us.
@@ -664,7 +458,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
 #pragma unroll
     for (int k = 0; k < P::PF; ++k) {
       pf[k] = make_uint4(0, 0, 0, 0);
-      if (src[k] >= 0) pf[k] = *reinterpret_cast<const uint4*>(base + src[k]);
+      if (src[k] >= 0) pf[k] = load16(base + src[k]);
     }
   };
   auto store = [&](int p) {
@@ -683,7 +477,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
 #pragma unroll
     for (int k = 0; k < WPT; ++k) {
       const int i = min(t + P::NT * k, WCH - 1), q = i % Q, co = (i / Q) % 32, tap = i / (Q * 32);
-      wr[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
+      wr[k] = load16(w + ((long long)tap * cout + co0 + co) * P::CIN + 8 * q);
     }
 #pragma unroll
     for (int k = 0; k < WPT; ++k) {
@@ -758,7 +552,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
     uint4 m[2];
     if (MASKED && put) {  // in flight while the next plane goes to LDS
 #pragma unroll
-      for (int g = 0; g < 2; ++g) m[g] = *reinterpret_cast<const uint4*>(relu_y + o + 16 * h + 8 * g);
+      for (int g = 0; g < 2; ++g) m[g] = load16(relu_y + o + 16 * h + 8 * g);
     }
     if constexpr (P::NBUF == 1) __syncthreads();  // every wave is done with the plane
     if (more) store(p + 1);
@@ -789,7 +583,7 @@ __global__ void __launch_bounds__(P::NT, P::NW / 4) conv_slide_kernel(
               u[g].z &= positive_mask(m[g].z);
               u[g].w &= positive_mask(m[g].w);
             }
-            *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = u[g];
+            store16(out + o + 16 * h + 8 * g, u[g]);
           }
       }
     }
@@ -860,15 +654,15 @@ inline void launch_slide32(const uint16_t* in, const uint16_t* w, const float* b
 // voxels, every load in flight at once and one barrier -- and forms ZT planes of 4 x 64 outputs from
 // it, one row per wave, 32 voxels at a time, with the weights of its 32 output channels in registers.
 //
-// The sums are in the order of conv_ring_kernel, bitwise: the K-steps (tap pairs with 8 channels,
+// The sums have a fixed order, that of the sliding kernel with 32 channels: the K-steps (tap pairs with 8 channels,
 // tap 2 k in lanes 0-31 and 2 k + 1 in the rest; taps with 16) fall into four chains of consecutive
 // steps, each summed from zero, and chain c of the tile w = 2 (y % 2) + x / 32 % 2 comes in the order
 // w, w - 1, w - 2, w - 3 modulo 4; the bias last.  With the order known per row parity and half, a
 // tile needs two accumulators.
 //
 // What bounds it is memory: 8 -> 32 on 1x256x64x64 moves 84 MB, 18 us at the rate of a large copy,
-// and takes 26 (FP32 result 31), where the ring kernel, whose waves pass partial sums to each other
-// for every 128 voxels, took 57; 16 -> 64 on 1x128x64x64 72 -> 42, 8 -> 32 on 128x32x32 17 -> 8 us.
+// and takes 26 (FP32 result 31), where a kernel whose waves passed partial sums to each other for
+// every 128 voxels took 57; 16 -> 64 on 1x128x64x64 72 -> 42, 8 -> 32 on 128x32x32 17 -> 8 us.
 template <int CIN_, int ZT_>
 struct BoxConv {
   static constexpr int CIN = CIN_, ZT = ZT_;
@@ -912,7 +706,7 @@ __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
     const int x = x0 + v - 1, y = y0 + r - 1, z = z0 + pz - 1;
     pf[k] = make_uint4(0, 0, 0, 0);
     if (it < P::CHUNKS && x >= 0 && x < W && y >= 0 && y < H && z >= 0 && z < D)
-      pf[k] = *reinterpret_cast<const uint4*>(in + (((nb * D + z) * H + y) * (long long)W + x) * CIN + 8 * q);
+      pf[k] = load16(in + (((nb * D + z) * H + y) * (long long)W + x) * CIN + 8 * q);
   }
   uint4 wb[P::KSTEPS];
 #pragma unroll
@@ -920,7 +714,7 @@ __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
     wb[k] = make_uint4(0, 0, 0, 0);
     const int tap = CIN == 8 ? 2 * k + h : k;
     if (tap < 27)
-      wb[k] = *reinterpret_cast<const uint4*>(w + ((long long)tap * cout + co0 + c) * CIN + (CIN == 8 ? 0 : 8 * h));
+      wb[k] = load16(w + ((long long)tap * cout + co0 + c) * CIN + (CIN == 8 ? 0 : 8 * h));
   }
   if (t < 32) sb[t] = bias ? bias[co0 + t] : 0.0f;
 #pragma unroll
@@ -969,7 +763,7 @@ __global__ void __launch_bounds__(P::NT, P::CIN == 8 ? 4 : 2) conv_box_kernel(
           pack_halves(sum, u);
           if (x < W)
 #pragma unroll
-            for (int g = 0; g < 2; ++g) *reinterpret_cast<uint4*>(out + o + 16 * h + 8 * g) = u[g];
+            for (int g = 0; g < 2; ++g) store16(out + o + 16 * h + 8 * g, u[g]);
         }
       }
     }
@@ -1109,7 +903,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
       const int y = y0 + r - 1, x = x0 + v;
       pd[k] = make_uint4(0, 0, 0, 0);
       if (it < DCH && z >= 0 && z < D && y >= 0 && y < H && x < W)
-        pd[k] = *reinterpret_cast<const uint4*>(base + ((long long)y * W + x) * cout + 8 * q);
+        pd[k] = load16(base + ((long long)y * W + x) * cout + 8 * q);
     }
   };
   auto store_dout = [&](int z) {
@@ -1128,7 +922,7 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
       const int y = y0 + r, x = x0 + v - 1;
       pi[k] = make_uint4(0, 0, 0, 0);
       if (it < ICH && y < H && x >= 0 && x < W && ci0 + 8 * q < cin)
-        pi[k] = *reinterpret_cast<const uint4*>(base + ((long long)y * W + x) * cin + 8 * q);
+        pi[k] = load16(base + ((long long)y * W + x) * cin + 8 * q);
     }
   };
   auto store_in = [&]() {
@@ -1621,41 +1415,22 @@ int conv_dispatch(const uint16_t* in, const uint16_t* w, const float* bias, cons
   const long long nvox = (long long)n * d * h * wd;
   hipStream_t s = S(stream);
   const bool small_plane = (long long)h * wd * cin < (1LL << 31);  // 32-bit offsets within an input plane
-  // the sliding and the box kernel move 16 bytes at a time
-  const bool slide = small_plane && aligned16(in) && aligned16(w) &&
-                     (out_f32 ? aligned16(out_f32) : aligned16(out)) && ((uintptr_t)relu_y & 15) == 0;
   switch (cin) {
-    case 8:
-      if (slide)  // (the box kernel applies no mask: the pass below does)
-        launch_box<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      else if (small_plane)
-        launch_ring<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      else
-        launch_conv<8>(in, w, bias, out, out_f32, d, h, wd, cout, relu, nvox, s);
-      break;
-    case 16:
-      if (slide)  // (the box kernel applies no mask: the pass below does)
-        launch_box<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      else if (small_plane)
-        launch_ring<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      else
-        launch_staged<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      break;
+    // (the box kernel applies no mask: the pass below does)
+    case 8: launch_box<8>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s); break;
+    case 16: launch_box<16>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s); break;
     case 32:
-      if (slide) {
+      if (small_plane) {
         launch_slide32(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
         return done();
       }
-      if (small_plane)
-        launch_ring<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
-      else
-        launch_staged<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
+      launch_staged<32>(in, w, bias, out, out_f32, n, d, h, wd, cout, relu, s);
       break;
     case 64:
       // few tiles: the staged kernel, whose blocks load no more than their own tile's share of the
       // weights and all three planes at once (1x5x9x33, 50 tiles x 2: 11 against 15 us; 1x64x16x16,
       // 512 x 2: 31 against 17)
-      if (slide && (long long)n * d * ((wd + 31) / 32) * ((h + 1) / 2) * (cout / 32) > 256) {
+      if (small_plane && (long long)n * d * ((wd + 31) / 32) * ((h + 1) / 2) * (cout / 32) > 256) {
         launch_slide<SlideConv<64, 1, 8, 1>>(in, w, bias, relu_y, out, out_f32, n, d, h, wd, cout, relu, s);
         return done();
       }
