@@ -840,10 +840,13 @@ constexpr int kWgX = 32, kWgY = 16;               // voxels and rows of a tile
 constexpr int kWgThreads = 512, kWgBlocks = 256;  // one resident block on each of 256 compute units
 constexpr int kWgRow = kWgX * 32, kWgPlane = (kWgY + 2) * kWgRow;  // elements of a staged dout row, plane
 
+constexpr int kSeg = 64;  // voxels of a row segment of wgrad_row_kernel
+
 struct WgradPlan {
   long long steps;  // (column, plane) pairs
   int nxb, nyb;     // tiles of a plane
   int nchunks, ci_tiles, tiles;
+  bool rows;        // a block per row segment (wgrad_row_kernel)
 };
 
 inline WgradPlan wgrad_plan(int n, int d, int h, int wd, int cin, int cout) {
@@ -855,7 +858,148 @@ inline WgradPlan wgrad_plan(int n, int d, int h, int wd, int cin, int cout) {
   p.tiles = (cout / 32) * p.ci_tiles;
   const long long want = (kWgBlocks + p.tiles - 1) / p.tiles;
   p.nchunks = (int)(want < p.steps ? want : p.steps);
+  // Few rows: tiles of 16 rows leave the device to a handful of blocks, each of which walks through its
+  // rows and adds up two groups, where a block per row segment is done after one (us, rows against tiles:
+  // 8 -> 32 on 3x17x33 9.9 and 15.0, 12x9x33 10.9 and 14.0; 32 -> 32 on 3x17x33 11.6 and 15.2).  Each
+  // leaves a partial sum, so that only so many pay (28x9x33, 8 -> 32 14.3 and 14.6), and fewer where a tile
+  // has at most 8 rows or 16 voxels and is done sooner itself (8x10x10, 16 -> 32 11.0 and 11.8, but
+  // 16x16x16, 8 -> 32 13.8 and 13.4; 3x5x5, 32 -> 32 9.5 and 10.1, but 40x5x5, 8 -> 32 12.8 and 10.8).
+  const long long rows = (long long)n * d * h * ((wd + kSeg - 1) / kSeg);
+  p.rows = cin <= 32 && rows * cin * cout <= (16384 << ((h > 8) + (wd > 16)));
+  if (p.rows) p.nchunks = (int)rows;
   return p;
+}
+
+// Small volumes (WgradPlan::rows): block (row segment, tile) of three waves owns a row of 64 voxels (x0 ..) and
+// the (co, ci) tile of 32 x 32; wave k accumulates the nine taps with dz = k - 1.  The block stages the
+// transposed row of dout, [co][x], into LDS, and each wave its three source rows (z + dz, y - 1 .. y + 1),
+// [ci][x] over x0 - 8 .. x0 + kSeg + 7.  The K order of an MFMA is free: lane half h takes voxels
+// x0 + 32 h + 8 s + j at step s, so that each lane walks its 32 voxels eight at a time and the dx = -1, +1
+// operands are its 16-byte words shifted by one element, the word before or after coming from the
+// previous or the next step.  Bound by the latency of one round of loads and of two launches.
+constexpr int kRsA = kSeg + 8;      // LDS row stride of the row of dout (elements; 36 dwords)
+constexpr int kRowB = kSeg + 16;    // staged source row
+constexpr int kRsB = kRowB + 8;     // LDS row stride of a source row (44 dwords)
+// Channel row r of a staged tile starts at r * stride + (r / 8) * 16 elements: the 8-dword shift per group
+// of 8 rows spreads the transposing stores of the four 8-channel groups over distinct banks.
+__host__ __device__ constexpr int trow(int r, int stride) { return r * stride + (r >> 3) * 16; }
+constexpr int kTileA = 32 * kRsA + 4 * 16, kTileB = 32 * kRsB + 4 * 16;  // elements
+
+// [p.e7, c.e0 .. c.e6] and [c.e1 .. c.e7, n.e0] of 8-element BF16 words (element 2i in the low half of
+// dword i)
+__device__ __forceinline__ uint4 shift_in_prev(uint4 p, uint4 c) {
+  return make_uint4((c.x << 16) | (p.w >> 16), (c.y << 16) | (c.x >> 16), (c.z << 16) | (c.y >> 16),
+                    (c.w << 16) | (c.z >> 16));
+}
+__device__ __forceinline__ uint4 shift_in_next(uint4 c, uint4 n) {
+  return make_uint4((c.x >> 16) | (c.y << 16), (c.y >> 16) | (c.z << 16), (c.z >> 16) | (c.w << 16),
+                    (c.w >> 16) | (n.x << 16));
+}
+
+__global__ void __launch_bounds__(192, 2) wgrad_row_kernel(const uint16_t* __restrict__ in,
+                                                           const uint16_t* __restrict__ dout, float* __restrict__ part,
+                                                           float* __restrict__ bpart, int D, int H, int W, int cin,
+                                                           int cout) {
+  __shared__ __align__(16) uint16_t sA[kTileA];
+  __shared__ __align__(16) uint16_t sB[3][3][kTileB];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, dz = wave - 1;
+  const int chunk = blockIdx.x, co0 = blockIdx.y * 32;  // one ci tile (cin <= 32)
+  const int nseg = (W + kSeg - 1) / kSeg;
+  const int y = chunk % H, x0 = chunk / H % nseg * kSeg, nz = chunk / H / nseg, z = nz % D;  // nz: n D + z
+
+  // 16-byte chunks two voxels at a time, so that the transposed stores are whole dwords (one channel of
+  // both voxels, paired by v_perm)
+  auto pair_store = [&](uint16_t* base, int stride, int q, int xi, const uint4& A, const uint4& B) {
+    const uint32_t a4[4] = {A.x, A.y, A.z, A.w}, b4[4] = {B.x, B.y, B.z, B.w};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      *reinterpret_cast<uint32_t*>(base + trow(8 * q + 2 * k, stride) + xi) = __builtin_amdgcn_perm(b4[k], a4[k], 0x05040100u);
+      *reinterpret_cast<uint32_t*>(base + trow(8 * q + 2 * k + 1, stride) + xi) =
+          __builtin_amdgcn_perm(b4[k], a4[k], 0x07060302u);
+    }
+  };
+  if (t < 128) {
+    const int q = t & 3, x = x0 + 2 * (t >> 2);
+    const uint16_t* src = dout + (((long long)nz * H + y) * W + x) * cout + co0 + 8 * q;
+    const uint4 none = make_uint4(0, 0, 0, 0), a = x < W ? load16(src) : none, b = x + 1 < W ? load16(src + cout) : none;
+    pair_store(sA, kRsA, q, 2 * (t >> 2), a, b);
+  }
+  constexpr int PB = (2 * kRowB + 63) / 64;  // voxel pairs per lane of a source row
+  for (int r = 0; r < 3; ++r) {
+    const int zz = z + dz, yy = y + r - 1;
+    const bool row_ok = zz >= 0 && zz < D && yy >= 0 && yy < H;
+    const long long base = ((long long)(nz + dz) * H + yy) * W;
+    uint4 buf[PB][2];
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      const int it = lane + 64 * k, q = it & 3, x = x0 - 8 + 2 * (it >> 2);
+      buf[k][0] = buf[k][1] = make_uint4(0, 0, 0, 0);
+      if (it < 2 * kRowB && row_ok && 8 * q < cin) {
+        const uint16_t* src = in + (base + x) * cin + 8 * q;
+        if (x >= 0 && x < W) buf[k][0] = load16(src);
+        if (x + 1 >= 0 && x + 1 < W) buf[k][1] = load16(src + cin);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      const int it = lane + 64 * k;
+      if (it < 2 * kRowB) pair_store(sB[wave][r], kRsB, it & 3, 2 * (it >> 2), buf[k][0], buf[k][1]);
+    }
+  }
+  __syncthreads();
+
+  const int h = lane >> 5, c = lane & 31;
+  const uint16_t* pa = sA + trow(c, kRsA) + 32 * h;
+  float bsum = 0.0f;  // wave 0, lane (h, c): channel co0 + c over voxels x0 + 32 h .. + 31
+  if (bpart && wave == 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float f[8];
+      unpack8(*reinterpret_cast<const uint4*>(pa + 8 * j), f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) bsum += f[i];
+    }
+  }
+  floatx16 acc[9];
+  const uint16_t* pb[3];
+  uint4 prv[3], cur[3];
+#pragma unroll
+  for (int dy = 0; dy < 3; ++dy) {
+    pb[dy] = sB[wave][dy] + trow(c, kRsB) + 32 * h;  // element 8 + 32 h is voxel x0 + 32 h
+    prv[dy] = *reinterpret_cast<const uint4*>(pb[dy]);
+    cur[dy] = *reinterpret_cast<const uint4*>(pb[dy] + 8);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) acc[3 * dy + k] = floatx16{};
+  }
+#pragma unroll
+  for (int st = 0; st < kSeg / 16; ++st) {
+    const uint4 a = *reinterpret_cast<const uint4*>(pa + 8 * st);
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy) {
+      const uint4 nxt = *reinterpret_cast<const uint4*>(pb[dy] + 16 + 8 * st);
+      acc[3 * dy + 0] = mfma16(a, shift_in_prev(prv[dy], cur[dy]), acc[3 * dy + 0]);  // voxels x - 1 ..
+      acc[3 * dy + 1] = mfma16(a, cur[dy], acc[3 * dy + 1]);
+      acc[3 * dy + 2] = mfma16(a, shift_in_next(cur[dy], nxt), acc[3 * dy + 2]);      // voxels x + 1 ..
+      prv[dy] = cur[dy];
+      cur[dy] = nxt;
+    }
+  }
+  // acc[3 dy + dx] row m = 8 (r / 4) + 4 h + r % 4 (co0 + m), column c
+  if (c < cin) {
+    float* dst = part + ((long long)chunk * 27 + 9 * wave) * cout * cin;
+#pragma unroll
+    for (int k = 0; k < 9; ++k)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        dst[((long long)k * cout + co0 + (r / 4) * 8 + 4 * h + (r & 3)) * cin + c] = acc[k][r];
+  }
+  if (bpart) {
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(&sB[0][0][0]);
+    if (t < 64) red[t] = bsum;
+    __syncthreads();
+    if (t < 32) bpart[(long long)chunk * cout + co0 + t] = red[t] + red[t + 32];
+  }
 }
 
 // Two transposing reads: the operand of 16 voxels x 32 channels that begins at `p` + this lane's
@@ -1484,7 +1628,10 @@ extern "C" int surr_conv3d_wgrad(const uint16_t* in, const uint16_t* dout, float
   // PACK8 has a third of the MFMAs but adds up eight waves' sums at the end, not two.  With one step
   // per block that is no gain: 8 -> 32 channels on 3x5x5 voxels 12.1 us with it and 9.7 without, on
   // 256x16x32 (256 steps) 21.1 and 21.0, on 256x16x64 24.8 and 28.0.
-  if (cin == 8 && p.steps > kWgBlocks)
+  if (p.rows)
+    hipLaunchKernelGGL(wgrad_row_kernel, grid, dim3(192), 0, S(stream), in, dout, part, dbias ? bpart : nullptr, d, h,
+                       wd, cin, cout);
+  else if (cin == 8 && p.steps > kWgBlocks)
     hipLaunchKernelGGL(wgrad_kernel<true>, grid, block, 0, S(stream), in, dout, part, dbias ? bpart : nullptr, d, h, wd,
                        cin, cout, p);
   else
