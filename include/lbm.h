@@ -104,8 +104,8 @@ lbm_status lbm_set_inflow(lbm_ctx *ctx, double xc, double yc, double diameter, d
 /* Tile shape of the step kernel: (tx, ty) in {(32, 4), (32, 8), (32, 16), (64, 4), (64, 8)}
  * cells per workgroup, zchunk >= 1 z planes per workgroup, or 0 to let the library choose
  * it from the number of workgroups the device holds at once.  By default the library chooses
- * (64, 4) or (32, 8), whichever covers the lattice with less work, and steps lattices of at most
- * 2^17 cells by small bricks instead of columns.  Results do not depend on the choice; this is a
+ * (64, 4), or (32, 8) where that saves enough work, and steps lattices of at most 2^17 cells by small
+ * bricks instead of columns unless they are flat.  Results do not depend on the choice; this is a
  * tuning hook.  LBM_EINVAL for other shapes or zchunk < 0. */
 lbm_status lbm_set_tiling(lbm_ctx *ctx, int tx, int ty, int zchunk);
 
@@ -253,9 +253,11 @@ lbm_status lbm_selftest_collide_host(const lbm_params *params, const double *fr,
  * j * tiles_x + i) receives for each tile how many times the step processes it as a tile of a
  * lattice without lateral walls (block 0), as an interior tile beside free-slip x or y faces (none
  * of its cells or ring cells lies on a wall: it takes the plain population loads, block 1) and as a
- * frame tile (it takes the loads that mirror at the walls, block 2).  One launch covers all tiles.
- * LBM_EDEVICE if an interior tile touches a wall (an internal error); LBM_EINVAL for invalid
- * parameters or shapes. */
+ * frame tile (it takes the loads that mirror at the walls, block 2).  One launch covers all tiles: the
+ * count comes from walking its grid, with one, some and all of its z chunks, through the map from
+ * blocks to tiles that the step kernel uses; a chunk processed any other number of times than once shows
+ * as its tile's count.  LBM_EDEVICE if a block falls outside of the lattice or an interior tile touches a
+ * wall (internal errors); LBM_EINVAL for invalid parameters or shapes. */
 lbm_status lbm_selftest_tile_sets_host(const lbm_params *params, int tx, int ty, int *counts);
 
 #ifdef __cplusplus

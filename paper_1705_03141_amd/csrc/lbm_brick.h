@@ -14,7 +14,7 @@
 // execute more than one of them.  What bounds a step is its latency (launch, one round of loads
 // from another XCD's writes, pull, collision) while every compute unit has one workgroup, and the
 // 2.5 pulls per cell beyond that.  Measured per step, FP32, against the marching kernel: 32^3 9.8
-// against 19.2 us, 41^3 21 against 23, 48^3 19.4 against 27.4; 64^3 40 against 31 (so not there).
+// against 19.2 us, 41^3 21 against 23, 48^3 19.4 against 27.4; 64^3 40 against 30.
 #pragma once
 
 #include "lbm_step.h"

@@ -10,7 +10,7 @@
 // memory, about 150 loads per cell.  Measured, coarse state with factor 1 of the FP32 jet
 // 256x256x1024 (128 B read and 16 B written per cell): 2.37 ms, 4.1 TB/s, against 11.3 ms; with
 // factor 4 of an FP16 jet 112x112x448, where one thread walked the 64 cells of a block:
-// 0.16 ms against 1.8 ms; diagnostics of an FP32 85^3 lattice 37 us against 79 us.
+// 0.16 ms against 1.8 ms; diagnostics of an FP32 85^3 lattice 30 us against 79 us.
 #pragma once
 
 #include "lbm_step.h"
@@ -23,6 +23,8 @@ struct ScanTile {
   static constexpr int KS = (NS + NT - 1) / NT;                 // per thread
 };
 
+// (Four waves per SIMD leave 128 registers: the diagnostics between lateral walls spill some 24 of them, 96 B
+// per lane, and the coarse state keeps its block sums, whose factor is a run-time value, in 32 B of scratch.)
 template <typename T, bool WALLS, int KIND>
 __global__ void __launch_bounds__(ScanTile::NT, 4) scan_kernel(const AuxArgs A, const ScanArgs R) {
   constexpr int TX = ScanTile::TX, TY = ScanTile::TY, NT = ScanTile::NT, SX = ScanTile::SX, NS = ScanTile::NS,

@@ -377,7 +377,7 @@ __device__ __forceinline__ void store_f32x16(float* o, const floatx16& v, int h)
 // c_w-3, indices modulo 4, w = 2 (y % 2) + x / 32 % 2; the bias comes last.  So the taps of a plane
 // are walked in order, and unfinished chains travel with their output: two accumulators per output
 // with 64 channels (sum and chain), up to four with 32, nine for the three planes, which leaves
-// room for one row per wave.
+// room for one row per wave (with 64 channels still 256 registers and 24 to 60 B per lane of scratch).
 //
 // The weights of the co tile stay in LDS in fragment order (1 KB per tap and 16 channels, read
 // without conflicts); the plane of voxels has a voxel stride of CIN + 8 elements (4 x an odd number
@@ -1078,8 +1078,10 @@ __global__ void __launch_bounds__(kWgThreads, 2) wgrad_kernel(const uint16_t* __
   };
 
   // The whole walk for one role.  LAST: the fourth wave of a group.  The two instances run side by
-  // side and meet at the same barriers, two per step and two per round of the reduction; each has
-  // its own accumulators (one code path for both kept them twice, and spilled).
+  // side and meet at the same barriers, two per step and two per round of the reduction: every barrier
+  // stands in code that both have, outside of what depends on LAST, and under conditions that hold for
+  // the whole block.  Each instance has its own accumulators (one code path for both kept them twice,
+  // and spilled).
   auto walk = [&](auto last) {
   constexpr bool LAST = decltype(last)::value;
   floatx16 acc[NACC], accb = floatx16{};
